@@ -14,7 +14,8 @@
 //
 // Two kernels:
 //  * gemm_ring   - prefill: BN x BM x 64 tiles copied straight into an LDS ring
-//                  of NS stages, 8 waves, 16x16x32 bf16 MFMA, XCD-aware order.
+//                  of NS stages, 8 waves, 16x16x32 bf16 MFMA, XCD-aware order;
+//                  256-token tiles run a ping-pong main loop.
 //  * gemm_skinny - decode (M <= 64 tokens): HBM-bound weight streaming, 2,
 //                  4 or 8 waves split K inside a workgroup, reduced through
 //                  LDS in a fixed order (deterministic).
@@ -28,6 +29,7 @@
 #include <algorithm>
 
 #include <string>
+#include <type_traits>
 
 namespace hs {
 
@@ -178,10 +180,12 @@ __device__ __forceinline__ void wait_vm() {
 
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// NW waves per workgroup as 2 x NW/2: two wave columns over the BN weight
-// rows, NW/2 wave rows over the BM tokens.
-template <int BN, int BM, int BK, int NS, int NW = 4>
+// Eight waves per workgroup, two per SIMD, as 2 x 4: two wave columns over the
+// BN weight rows, four wave rows over the BM tokens.
+constexpr int kRingWaves = 8;
+template <int BN, int BM, int BK, int NS>
 struct RTile {
+  static constexpr int NW = kRingWaves;
   static constexpr int CPR = BK / 8;           // 16-byte chunks per row
   static constexpr int RPI = 64 / CPR;         // rows per load instruction
   static constexpr int WN = BN / 2, WM = BM / (NW / 2), TN = WN / 16, TM = WM / 16;
@@ -189,7 +193,6 @@ struct RTile {
   static constexpr int LPS = WI + XI;          // loads per stage per wave
   static constexpr int W_BYTES = BN * BK * 2, STAGE = (BN + BM) * BK * 2;
   static_assert(BK == 64, "weights come in 64-column slabs");
-  static_assert(NW == 4 || NW == 8, "4 or 8 waves");
   static_assert(WI >= 1 && XI >= 1 && TM >= 1, "tile too small for the waves");
 };
 
@@ -213,28 +216,23 @@ __device__ __forceinline__ bf16x8_v lds_frag(const bf16_t* s, int r, int c) {
 }
 
 // How many row tiles ahead of its MFMAs a wave reads the A fragments: three
-// for the 4- and 6-row-tile wave tiles (128 x 128 and 192-row tiles; 512-token
-// 7B shapes, MI355X: gate/up 96.6 -> 94.0 us, QKV 55.8 -> 53.8, o 29.3 ->
-// 28.2), one for the 8-row-tile ones of 256-row tiles (three made 8192-token
-// launches 1-4 % slower). The fragments and MFMAs are the same either way.
+// for the 4- and 6-row-tile wave tiles (128 x 128 and 192 x 128 tiles;
+// 512-token 7B shapes, MI355X: QKV 55.8 -> 53.8 us, o 29.3 -> 28.2), one for
+// the 8-row-tile ones of 256-row tiles. The fragments and MFMAs are the same
+// either way.
 template <int TN>
 constexpr int ring_pd() {
   return (TN == 4 || TN == 6) ? 3 : 1;
 }
 
-template <int BN, int BM, int BK, int NS, int NW, int TN, int TM, int PD, typename Dma>
+template <int BN, int BM, int BK, int NS, int TN, int TM, int PD, typename Dma>
 __device__ __forceinline__ void ring_stage(f32x4_v (&acc)[TN][TM], bf16x8_v (&a)[PD + 1],
                                            bf16x8_v (&b)[2][TM], const bf16_t* sw,
                                            const bf16_t* sx, int wn, int wm, int fr, int g,
                                            bool pending, Dma&& dma) {
-  using T = RTile<BN, BM, BK, NS, NW>;
+  using T = RTile<BN, BM, BK, NS>;
   constexpr int CPR = T::CPR, KS = BK / 32, NT = TN * KS;
   constexpr int MASK_MFMA = 0x008, MASK_DS_READ = 0x100;
-  // 256 x 256 tiles: a wave runs its MFMA groups at raised priority, so the
-  // SIMD's other wave issues its LDS reads and loads in between instead of
-  // competing with them (8192 tokens, MI355X: gate/up 1155-1162 -> 1107-1113
-  // us, down 580 -> 562; the smaller tiles gained nothing)
-  constexpr bool PRIO = BN == 256 && BM == 256 && NW == 8;
   // row tile t of the stage (t = ks TN + i) uses A slot t mod (PD + 1); the
   // deferred last one must not share a slot with the next stage's first PD
   static_assert(KS == 2 && NT % (PD + 1) == 0, "A fragment slots");
@@ -269,11 +267,9 @@ __device__ __forceinline__ void ring_stage(f32x4_v (&acc)[TN][TM], bf16x8_v (&a)
         b[(ks + 1) & 1][j] = lds_frag<CPR>(sx, wm * T::WM + j * 16 + fr, (ks + 1) * 4 + g);
     }
     if (t == NT - 1) break;  // deferred to the next stage (or the end)
-    if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int j = 0; j < TM; ++j)
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t % (PD + 1)], b[ks & 1][j], acc[i][j], 0, 0, 0);
-    if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
     if (ra && rb) __builtin_amdgcn_sched_group_barrier(MASK_DS_READ, TM + 1, 0);
     else if (ra) __builtin_amdgcn_sched_group_barrier(MASK_DS_READ, 1, 0);
     else if (rb) __builtin_amdgcn_sched_group_barrier(MASK_DS_READ, TM, 0);
@@ -315,22 +311,180 @@ __device__ __forceinline__ int sk_owner(int64_t i, int64_t total, int G) {
   return (int)(((i + 1) * G - 1) / total);
 }
 
-// NS weight stages and NSX activation stages (NSX = NS, or one more or one
-// fewer with two stages of the other): the loads of weight slab j + NS - 1
-// and activation slab j + NSX - 1 are in flight while slab j is multiplied.
-template <int BN, int BM, int NS, int SPR, bool SK, int EPI, int NW = 4, int NSX = NS>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
+// Ping-pong main loop (eight waves, two stages of both operands): acc = sum
+// over 64-k slabs [k0, k1) of tile (n0, m0), every output summed by one wave in
+// k order.
+//
+// A slab is multiplied in four phases of TNH x TMH x 2 MFMAs (a quarter of the
+// wave's tile), each preceded by the LDS reads it adds. Waves 4 .. 7 run one
+// barrier behind waves 0 .. 3, and wave w shares a SIMD with wave w + 4, so one
+// of a SIMD's two waves always multiplies (at raised priority) while the
+// other reads LDS and issues loads. Wave slab s, phase p reads: 0: rows' first
+// half A0 and tokens' first half B0, 1: B1, 2: A1 (over A0), 3: nothing; and
+// multiplies A0 B0, A0 B1, A1 B1, A1 B0.
+//
+// Between two barriers ("slots"), waves 0 .. 3 read in slot 2p and multiply in
+// slot 2p + 1, waves 4 .. 7 one slot later. A region read in phase p is
+// consumed by that phase's MFMAs, so every wave is done with it by the end of
+// slot 2p + 2, and loads into it may be issued from phase p + 2 (slot 2p + 4
+// or 2p + 5): slab s + 2's A0 and B0 in phase 2 of slab s, its B1 in phase 3,
+// its A1 in phase 0 of slab s + 1. Whatever phase p reads has been waited for by
+// the wave that loaded it at the end of its phase p - 1, before the barrier
+// that opens slot 2p. A load has five to six phases (1300 cycles or more at
+// 256 x 256) to land and up to 14 KiB per wave are in flight.
+template <int BN, int BM, int TN, int TM, typename F>
+__device__ __forceinline__ void pp_mainloop(f32x4_v (&acc)[TN][TM], const GemmArgs& a,
+                                            const v4i_t& rw, const v4i_t& rx, const char* smem,
+                                            uint32_t lds0, int n0, int m0, int k0, int k1,
+                                            int lane, int wave, F&& after_issue) {
+  constexpr int TNH = TN / 2, TMH = TM / 2, WN = BN / 2, WM = BM / 4;
+  constexpr int W_BYTES = BN * 128, X_BYTES = BM * 128;
+  static_assert(TN * 16 == WN && TM * 16 == WM && TN % 2 == 0 && TM % 2 == 0, "2 x 4 waves");
+  static_assert(TNH == 3 || TNH == 4, "blocks of a half over eight waves");
+  const int wn = wave & 1, wm = wave >> 1, fr = lane & 15, g = lane >> 4;
+  const bool late = wave >= 4;
+  // 8-row blocks of a half of the weight tile: 4 TNH over eight waves, two
+  // each (TNH = 4); with 12, waves 0 .. 3 take two of the first half and one
+  // of the second, waves 4 .. 7 the other way round
+  constexpr int A0 = TNH == 4 ? 2 : 1, AS = TNH == 4 ? 4 : 3;  // fewest of a half; of both halves
+  int blk[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      int b;
+      if constexpr (TNH == 4) b = 2 * wave + q;
+      else b = (h == 1) == late ? 2 * (wave & 3) + q : 8 + (wave & 3);
+      blk[h][q] = (b / (2 * TNH)) * (4 * TNH) + h * 2 * TNH + b % (2 * TNH);
+    }
+  const int sw_slab = (a.N / 8) * 1024, nb = a.N / 8 - 1;
+  auto issue_a = [&](int h, int buf, int kt) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (TNH == 3 && q == 1 && (h == 1) != late) continue;  // uniform: one block of this half
+      dma16(rw, lane * 16, min(n0 / 8 + blk[h][q], nb) * 1024 + kt * sw_slab,
+            lds0 + buf * W_BYTES + blk[h][q] * 1024);
+    }
+  };
+  // activations: 8 TMH blocks of 8 tokens per half, TMH per wave (rows past
+  // the last re-read it; their outputs are not stored)
+  int vx[2][TMH];
+  uint32_t lx[2][TMH];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < TMH; ++q) {
+      const int b = TMH * wave + q;
+      const int row = (b / (2 * TMH)) * WM + h * 16 * TMH + (b % (2 * TMH)) * 8;
+      const int r = lane >> 3;
+      vx[h][q] = (min(m0 + row + r, a.M - 1) * (int)a.ldx + ((lane & 7) ^ r) * 8) * 2;
+      lx[h][q] = lds0 + 2 * W_BYTES + row * 128;
+    }
+  auto issue_x = [&](int h, int buf, int kt) {
+#pragma unroll
+    for (int q = 0; q < TMH; ++q) dma16(rx, vx[h][q], kt * 128, lx[h][q] + buf * X_BYTES);
+  };
+  // fragment addresses: row fr of a 16-row tile, chunk 4 ks + g at (4 ks + g) ^ (row & 7)
+  const int swz = (g ^ (fr & 7)) * 16;
+  const int fw = (wn * WN + fr) * 128 + swz, fx = 2 * W_BYTES + (wm * WM + fr) * 128 + swz;
+  bf16x8_v fa[TNH][2], fb[2][TMH][2];
+  auto read_a = [&](int h, int buf) {
+    const char* p0 = smem + (fw + buf * W_BYTES);
+    const char* p1 = smem + ((fw ^ 64) + buf * W_BYTES);
+#pragma unroll
+    for (int i = 0; i < TNH; ++i) {
+      fa[i][0] = as_bf16x8(ld16(p0 + (h * TNH + i) * 2048));
+      fa[i][1] = as_bf16x8(ld16(p1 + (h * TNH + i) * 2048));
+    }
+  };
+  auto read_b = [&](int h, int buf) {
+    const char* p0 = smem + (fx + buf * X_BYTES);
+    const char* p1 = smem + ((fx ^ 64) + buf * X_BYTES);
+#pragma unroll
+    for (int i = 0; i < TMH; ++i) {
+      fb[h][i][0] = as_bf16x8(ld16(p0 + (h * TMH + i) * 2048));
+      fb[h][i][1] = as_bf16x8(ld16(p1 + (h * TMH + i) * 2048));
+    }
+  };
+  auto slot = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    wg_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int ha, int hb) {
+    slot();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < TNH; ++i)
+#pragma unroll
+        for (int j = 0; j < TMH; ++j)
+          acc[ha * TNH + i][hb * TMH + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              fa[i][ks], fb[hb][j][ks], acc[ha * TNH + i][hb * TMH + j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    slot();
+  };
+  const int n = k1 - k0;
+  // one slab; LEFT = slabs after it (2 = two or more): which loads are still
+  // to be issued and how many of this wave's may be outstanding at each wait
+  auto slab = [&](int j, auto left) {
+    constexpr int LEFT = decltype(left)::value;
+    const int buf = j & 1;
+    read_b(0, buf);
+    read_a(0, buf);
+    if constexpr (LEFT >= 1) issue_a(1, buf ^ 1, k0 + j + 1);
+    // B1 of this slab: later are its A1 and the next slab's four parts
+    wait_vm<(LEFT >= 1 ? A0 + AS + 2 * TMH : A0)>();
+    multiply(0, 0);
+    read_b(1, buf);
+    wait_vm<(LEFT >= 1 ? AS + 2 * TMH : 0)>();  // A1 of this slab
+    multiply(0, 1);
+    read_a(1, buf);
+    if constexpr (LEFT >= 2) {
+      issue_a(0, buf, k0 + j + 2);
+      issue_x(0, buf, k0 + j + 2);
+    }
+    multiply(1, 1);
+    if constexpr (LEFT >= 2) issue_x(1, buf, k0 + j + 2);
+    // A0 and B0 of the next slab
+    if constexpr (LEFT >= 1) wait_vm<(LEFT >= 2 ? AS + 3 * TMH : A0 + TMH)>();
+    multiply(1, 0);
+  };
+  issue_a(0, 0, k0);
+  issue_x(0, 0, k0);
+  issue_x(1, 0, k0);
+  issue_a(1, 0, k0);
+  if (n > 1) {
+    issue_a(0, 1, k0 + 1);
+    issue_x(0, 1, k0 + 1);
+    issue_x(1, 1, k0 + 1);
+  }
+  after_issue();
+  if (n > 1) wait_vm<AS + 3 * TMH>();
+  else wait_vm<A0 + TMH>();
+  wg_barrier();
+  if (late) wg_barrier();
+  for (int j = 0; j < n - 2; ++j) slab(j, std::integral_constant<int, 2>{});
+  if (n > 1) slab(n - 2, std::integral_constant<int, 1>{});
+  slab(n - 1, std::integral_constant<int, 0>{});
+  if (!late) wg_barrier();
+}
+
+// NS stages of both operands: the loads of slab j + NS - 1 are in flight while
+// slab j is multiplied. PP: the ping-pong main loop instead.
+template <int BN, int BM, int NS, int SPR, bool SK, int EPI, bool PP>
+__global__ __launch_bounds__(64 * kRingWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_ring(GemmArgs a, GemmSched sc) {
-  constexpr int BK = 64;
-  using T = RTile<BN, BM, BK, NS, NW>;
-  static_assert(NSX == NS || (NS == 2 && NSX == 3) || (NS == 3 && NSX == 2),
-                "stage counts: equal, or 2 and 3");
+  constexpr int BK = 64, NW = kRingWaves;
+  using T = RTile<BN, BM, BK, NS>;
+  static_assert(!PP || NS == 2, "the ping-pong loop has two stages");
   constexpr int CPR = T::CPR, RPI = T::RPI, WN = T::WN, WM = T::WM, TN = T::TN, TM = T::TM;
   constexpr int LPS = T::LPS;
   static_assert((EPI != EPI_SWIGLU && EPI != EPI_QKV_ROPE) || (WN % 32) == 0,
                 "SwiGLU and RoPE need 32-row pairs");
   constexpr int X_BYTES = BM * BK * 2;
-  __shared__ __attribute__((aligned(1024))) char smem[NS * T::W_BYTES + NSX * X_BYTES];
+  __shared__ __attribute__((aligned(1024))) char smem[NS * (T::W_BYTES + X_BYTES)];
   __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -364,9 +518,9 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
   // loads only make the vmcnt waits of the ring stricter: loads complete in
   // order.)
   constexpr bool ROPE_PRE = EPI == EPI_QKV_ROPE && !SK;
-  // (the cos/sin rows take 4 TN TM registers: with eight waves, two per
-  // SIMD, only the small tiles have room; 256 x 256 spilled 100 registers)
-  constexpr bool ROPE_TAB = ROPE_PRE && TN * TM <= (NW == 4 ? 32 : 16);
+  // (the cos/sin rows take 4 TN TM registers: only the small tiles have room;
+  // 256 x 256 spilled 100 registers)
+  constexpr bool ROPE_TAB = ROPE_PRE && TN * TM <= 16;
   constexpr int RJ = ROPE_PRE ? TM : 1, RJT = ROPE_TAB ? TM : 1, RI = ROPE_TAB ? TN / 2 : 1;
   int r_pos[RJ], r_slot[RJ];
   float4 r_cos[RJT][RI], r_sin[RJT][RI];
@@ -399,98 +553,65 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
     for (int i = 0; i < TN; ++i)
 #pragma unroll
       for (int j = 0; j < TM; ++j) acc[i][j] = f32x4_v{0.f, 0.f, 0.f, 0.f};
+    if constexpr (PP) {
+      pp_mainloop<BN, BM>(acc, a, rw, rx, smem, lds0, n0, m0, k0, k1, lane, wave_u, after_issue);
+      return;
+    } else {
     // weights: block (kt, n0/8 + wave * BN/(8 NW) + q) of the tiled format
     const int sw_base = (n0 / 8 + wave_u * (BN / NW / 8)) * 1024;
     const int vx = ((m0 + wave * (BM / NW) + lrow) * (int)a.ldx + lchunk * 8) * 2;
-    // load q of a step (0 <= q < LPS): the operand whose slab is due sooner
-    // goes first (weights when the look-aheads are equal)
-    constexpr int AW = NS - 1, AX = NSX - 1;          // look-ahead in steps
-    constexpr bool XFIRST = AX < AW;
-    constexpr int FIRST = XFIRST ? T::XI : T::WI, SECOND = LPS - FIRST;
-    auto issue_w = [&](int stage, int kt, int q) {
-      dma16(rw, vw, sw_base + kt * sw_slab + q * 1024, lds_w + stage * T::W_BYTES + q * 1024);
-    };
-    auto issue_x = [&](int stage, int kt, int q) {
-      dma16(rx, vx, q * sx_step + kt * BK * 2, lds_x + stage * X_BYTES + q * 1024);
+    // load q of a step (0 <= q < LPS): weights first
+    constexpr int AHEAD = NS - 1;  // look-ahead in steps
+    auto issue = [&](int j, int q) {
+      const int stage = j % NS, kt = k0 + j;
+      if (q < T::WI)
+        dma16(rw, vw, sw_base + kt * sw_slab + q * 1024, lds_w + stage * T::W_BYTES + q * 1024);
+      else
+        dma16(rx, vx, (q - T::WI) * sx_step + kt * BK * 2,
+              lds_x + stage * X_BYTES + (q - T::WI) * 1024);
     };
     // the loads of a step are spread over the first SPR/4 of the row-tile
     // steps of the current slab's multiplication
     constexpr int STEPS = TN * (BK / 32), USE = STEPS * SPR / 4;
     static_assert(USE >= 1, "spread");
-    auto issue_part = [&](int j, int step, bool more_w, bool more_x) {
-      if (step < USE) {
-#pragma unroll
-        for (int q = step * LPS / USE; q < (step + 1) * LPS / USE; ++q) {
-          const bool first = q < FIRST;
-          const bool is_x = first == XFIRST;
-          const int qq = first ? q : q - FIRST;
-          if (is_x) {
-            if (more_x) issue_x((j + AX) % NSX, k0 + j + AX, qq);
-          } else if (more_w) {
-            issue_w((j + AW) % NS, k0 + j + AW, qq);
-          }
-        }
-      }
-    };
-    // Step j issues the loads of weight slab j + AW and activation slab
-    // j + AX while it multiplies slab j. The issue is behind a (uniform)
-    // branch on purpose: it splits the step into scheduling regions, without
-    // which the register allocator shuffles the accumulators between MFMAs.
-    // Loads complete in issue order, so before slab j + 1 the wave waits
-    // until only the loads issued after slab j + 1's last one are
-    // outstanding: with equal look-aheads the (AW - 1) later steps' loads,
-    // else the second operand's loads of step j.
+    // Step j issues the loads of slab j + NS - 1 while it multiplies slab j.
+    // The issue is behind a (uniform) branch on purpose: it splits the step
+    // into scheduling regions, without which the register allocator shuffles
+    // the accumulators between MFMAs. Loads complete in issue order, so before
+    // slab j + 1 the wave waits until only the loads of the NS - 2 later slabs
+    // are outstanding.
     const int n = k1 - k0;
-    // prologue: the loads of the virtual steps -max(AW, AX) .. -1, in the
-    // same order as the steady state
 #pragma unroll
-    for (int v = -(AW > AX ? AW : AX); v < 0; ++v) {
-      const int tw = v + AW, tx = v + AX;   // slabs this virtual step loads
-      auto w_part = [&] {
-        if (tw >= 0 && tw < n)
+    for (int t = 0; t < AHEAD; ++t)
+      if (t < n)
 #pragma unroll
-          for (int q = 0; q < T::WI; ++q) issue_w(tw % NS, k0 + tw, q);
-      };
-      auto x_part = [&] {
-        if (tx >= 0 && tx < n)
-#pragma unroll
-          for (int q = 0; q < T::XI; ++q) issue_x(tx % NSX, k0 + tx, q);
-      };
-      if (XFIRST) { x_part(); w_part(); } else { w_part(); x_part(); }
-    }
+        for (int q = 0; q < LPS; ++q) issue(t, q);
     after_issue();
-    // before slab 0: what the prologue issued after slab 0's loads
-    if constexpr (AW == AX) {
-      if (n >= NS - 1) wait_vm<(NS - 2) * LPS>();
-      else wait_vm<0>();
-    } else {
-      if (n >= 2) wait_vm<SECOND>();
-      else wait_vm<0>();
-    }
+    if (n >= AHEAD) wait_vm<(NS - 2) * LPS>();
+    else wait_vm<0>();
     wg_barrier();
     constexpr int PD = ring_pd<TN>();
     bf16x8_v fa[PD + 1], fb[2][TM];
     for (int j = 0; j < n; ++j) {
-      const bool more_w = j + AW < n, more_x = j + AX < n;
+      const bool more = j + AHEAD < n;
       const bf16_t* sw = reinterpret_cast<const bf16_t*>(smem + (j % NS) * T::W_BYTES);
       const bf16_t* sx =
-          reinterpret_cast<const bf16_t*>(smem + NS * T::W_BYTES + (j % NSX) * X_BYTES);
-      ring_stage<BN, BM, BK, NS, NW, TN, TM, PD>(acc, fa, fb, sw, sx, wn, wm, fr, g, j > 0, [&](int step) {
-        issue_part(j, step, more_w, more_x);
+          reinterpret_cast<const bf16_t*>(smem + NS * T::W_BYTES + (j % NS) * X_BYTES);
+      ring_stage<BN, BM, BK, NS, TN, TM, PD>(acc, fa, fb, sw, sx, wn, wm, fr, g, j > 0, [&](int step) {
+        if (more && step < USE) {
+#pragma unroll
+          for (int q = step * LPS / USE; q < (step + 1) * LPS / USE; ++q) issue(j + AHEAD, q);
+        }
       });
-      if constexpr (AW == AX) {
-        if (more_w) wait_vm<(NS - 2) * LPS>();
-        else wait_vm<0>();
-      } else {
-        if (more_w && more_x) wait_vm<SECOND>();
-        else wait_vm<0>();
-      }
+      if (more) wait_vm<(NS - 2) * LPS>();
+      else wait_vm<0>();
       wg_barrier();
     }
     // the last stage's deferred row tile
 #pragma unroll
     for (int jj = 0; jj < TM; ++jj)
       acc[TN - 1][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[(2 * TN - 1) % (PD + 1)], fb[1][jj], acc[TN - 1][jj], 0, 0, 0);
+    }
   };
 
   auto epilogue = [&](int n0, int m0) {
@@ -909,15 +1030,15 @@ hipError_t dispatch_skinny1(const GemmArgs& a, int epi, int nf, int u, int wv, b
   return hipErrorInvalidValue;
 }
 
-template <int BN, int BM, int NS, int SPR, bool SK, int NW = 4, int NSX = NS>
+template <int BN, int BM, int NS, int SPR, bool SK, bool PP = false>
 hipError_t dispatch_ring(const GemmArgs& a, int epi, const GemmSched& sc, int grid, hipStream_t s) {
-  const dim3 blk(64 * NW);
+  const dim3 blk(64 * kRingWaves);
   switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_STORE, NW, NSX>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_RESID, NW, NSX>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_SWIGLU, NW, NSX>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_F32: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_F32, NW, NSX>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_QKV_ROPE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_QKV_ROPE, NW, NSX>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_STORE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_STORE, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_RESID: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_RESID, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_SWIGLU, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_F32, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_QKV_ROPE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_QKV_ROPE, PP>), dim3(grid), blk, 0, s, a, sc); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -928,53 +1049,26 @@ struct RingCfg {
   int bn, bm;
   bool sk_ok;  // has a stream-K build
 };
-const RingCfg kRing[] = {{"256x256", 256, 256, false}, {"256x128", 256, 128, true},
+const RingCfg kRing[] = {{"256x256", 256, 256, false}, {"256x128", 256, 128, false},
                          {"128x128", 128, 128, true},  {"192x256", 192, 256, false},
                          {"192x128", 192, 128, false}};
 
-// 256 x 256: 2 stages (128 KiB of LDS); 192 x 256: 3 weight stages and 2
-// activation stages (136 KiB); the next slabs' loads issued in the first
-// half of the current one's multiplication. 256 x 128: 3 stages, loads
-// spread over the whole step. 192 x 128 (160 KiB) and 128 x 128: 4 stages.
+// 256 x 256 and 192 x 256: ping-pong loop (128 and 112 KiB of LDS). Same box,
+// MI355X, one-barrier loop -> ping-pong: 8192 tokens QKV 616 -> 591 us, o 219 ->
+// 210, gate/up 1093 -> 1040, down 560 -> 522; 15646 tokens 8B gate/up 2822 ->
+// 2688, down 1428 -> 1317; 512 tokens gate/up 87.4 -> 86.5. With operands of
+// zeros, which hold the clock up, 8192-token gate/up goes 929 -> 823 us (1.80
+// PFLOP/s): on real data the power limit takes half of the gain.
+// 256 x 128: 3 stages, loads spread over the whole step. 192 x 128 (160 KiB)
+// and 128 x 128: 4 stages.
 hipError_t launch_ring(const RingCfg& c, const GemmArgs& a, int epi, const GemmSched& sc,
                        int grid, hipStream_t s) {
-  // Eight waves (two per SIMD: one wave's LDS reads and barrier waits hide
-  // behind the other's MFMAs) unless HS_GEMM_WAVES=4 (tuning only). The
-  // 512-token 7B stage, MI355X: o 36.5 -> 32.9 us, down 69.8 -> 65.5, QKV
-  // 66.7 -> 59.7, gate/up unchanged; 8192 tokens: o 240 -> 219, QKV 674 -> 647.
-  // Each output is still summed by one wave in k order, so the bits do not
-  // change.
-  static const char* waves = getenv("HS_GEMM_WAVES");
-  const bool w4 = waves && atoi(waves) == 4;
-  if (c.bn == 256 && c.bm == 256)
-    return w4 ? dispatch_ring<256, 256, 2, 2, false>(a, epi, sc, grid, s)
-              : dispatch_ring<256, 256, 2, 2, false, 8>(a, epi, sc, grid, s);
-  // 192 x 256: three weight stages and two activation stages (136 KiB),
-  // the weights requested two slabs ahead. At a 512-token prompt every CU
-  // runs one tile and each 64-k slab takes about 1.3 us, shorter than a
-  // load's latency under load: 7B gate/up 91.0 -> 82.0 us (two of each:
-  // 112 KiB; weights two ahead and activations one gave the same gain as
-  // the reverse, and three of each does not fit). At 8192 tokens the
-  // 256 x 256 tiles' longer slabs hide the latency: a third weight stage
-  // there moved nothing beyond noise.
-  if (c.bn == 192 && c.bm == 256)
-    return w4 ? dispatch_ring<192, 256, 2, 2, false>(a, epi, sc, grid, s)
-              : dispatch_ring<192, 256, 3, 2, false, 8, 2>(a, epi, sc, grid, s);
-  if (c.bn == 192 && c.bm == 128)
-    return w4 ? dispatch_ring<192, 128, 4, 4, false>(a, epi, sc, grid, s)
-              : dispatch_ring<192, 128, 4, 4, false, 8>(a, epi, sc, grid, s);
-  if (c.bn == 256 && c.bm == 128) {
-    // stream-K 256 x 128 keeps four waves (its partial-tile reduction does
-    // not fit the registers of eight: 125-138 spilled)
-    if (sc.sk) return dispatch_ring<256, 128, 3, 4, true>(a, epi, sc, grid, s);
-    return w4 ? dispatch_ring<256, 128, 3, 4, false>(a, epi, sc, grid, s)
-              : dispatch_ring<256, 128, 3, 4, false, 8>(a, epi, sc, grid, s);
-  }
-  if (w4)
-    return sc.sk ? dispatch_ring<128, 128, 4, 4, true>(a, epi, sc, grid, s)
-                 : dispatch_ring<128, 128, 4, 4, false>(a, epi, sc, grid, s);
-  return sc.sk ? dispatch_ring<128, 128, 4, 4, true, 8>(a, epi, sc, grid, s)
-               : dispatch_ring<128, 128, 4, 4, false, 8>(a, epi, sc, grid, s);
+  if (c.bn == 256 && c.bm == 256) return dispatch_ring<256, 256, 2, 2, false, true>(a, epi, sc, grid, s);
+  if (c.bn == 192 && c.bm == 256) return dispatch_ring<192, 256, 2, 2, false, true>(a, epi, sc, grid, s);
+  if (c.bn == 192 && c.bm == 128) return dispatch_ring<192, 128, 4, 4, false>(a, epi, sc, grid, s);
+  if (c.bn == 256 && c.bm == 128) return dispatch_ring<256, 128, 3, 4, false>(a, epi, sc, grid, s);
+  return sc.sk ? dispatch_ring<128, 128, 4, 4, true>(a, epi, sc, grid, s)
+               : dispatch_ring<128, 128, 4, 4, false>(a, epi, sc, grid, s);
 }
 
 int device_cus() {

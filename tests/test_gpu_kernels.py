@@ -104,6 +104,40 @@ def test_gemm_staged_activations_bitwise(M, N, K):
     assert np.abs(outs[1] - ref).max() <= 8e-3 * np.abs(ref).max()
 
 
+# The ping-pong main loop at its edges: one, two, three and four 64-k slabs
+# (its peeled ends), a K that is no multiple of 64, rows and columns one past,
+# one short of and far from a tile's end.
+@pytest.mark.parametrize("cfg", ["256x256,dp", "192x256,dp"])
+@pytest.mark.parametrize("M,N,K", [(65, 16, 64), (257, 208, 128), (255, 400, 192), (512, 256, 256),
+                                   (300, 1376, 688), (769, 272, 320)])
+@pytest.mark.parametrize("epi", ["resid", "f32"])
+def test_gemm_ping_pong_edges(cfg, M, N, K, epi, monkeypatch):
+    torch = G.torch()
+    hs = _hs()
+    rng = np.random.default_rng(M + N + K)
+    X = gen.round_to_bf16(rng.standard_normal((M, K)).astype(np.float32))
+    Wt = gen.round_to_bf16((rng.standard_normal((N, K)) * 0.05).astype(np.float32))
+    kp = -(-K // 64) * 64
+    Xp = np.zeros((M, kp), np.float32)
+    Xp[:, :K] = X
+    dX = G.to_dev_bf16(Xp)
+    dW = torch.from_numpy(G.tile_bits(gen.to_bf16_bits(Wt)).view(np.int16)).cuda()
+    ref = X.astype(np.float64) @ Wt.astype(np.float64).T
+    if epi == "resid":
+        R = gen.round_to_bf16(rng.standard_normal((M, N)).astype(np.float32))
+        Y = G.to_dev_bf16(R)
+        ref = R + ref
+    else:
+        Y = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    monkeypatch.setenv("HS_GEMM_CFG", cfg)
+    hs.hs_k_gemm(dX.data_ptr(), kp, dW.data_ptr(), Y.data_ptr(), N,
+                 Y.data_ptr() if epi == "resid" else 0, N, M, N, K, epi, G.stream_ptr())
+    torch.cuda.synchronize()
+    out = Y.cpu().numpy() if epi == "f32" else G.from_dev_bf16(Y)
+    # one bf16 rounding of the result (2^-9 of it) and float32 sums
+    assert np.abs(out - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
+
+
 # 7B-shape projections at a 512-token prompt: few output tiles, so their k
 # ranges are split across workgroups (stream-K). Rows are sampled for the
 # float64 reference; two calls must agree bitwise.
