@@ -18,15 +18,17 @@ __device__ __forceinline__ float bf2f(bf16_t b) {
   return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
-// float -> bf16, round to nearest even (finite inputs).
-__device__ __forceinline__ bf16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return static_cast<bf16_t>(u >> 16);
+// float -> bf16, round to nearest even: one v_cvt_pk_bf16_f32 for two values,
+// where integer arithmetic takes about ten VALU instructions (the same bits for
+// every finite value; a NaN stays a NaN).
+typedef __bf16 bf16x2_v __attribute__((ext_vector_type(2)));
+typedef float f32x2_v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_v{lo, hi}), bf16x2_v));
 }
 
-__device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
-  return static_cast<uint32_t>(f2bf(lo)) | (static_cast<uint32_t>(f2bf(hi)) << 16);
+__device__ __forceinline__ bf16_t f2bf(float f) {
+  return static_cast<bf16_t>(pack2bf(f, 0.f));
 }
 
 __device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
