@@ -29,7 +29,7 @@ extern "C" {
  * of X zero. This is the projection arithmetic of every decoder layer (QKV,
  * O, gate/up, down) and of the LM head. Shapes with few output tiles split
  * their k range over workgroups; the partial sums go through a workspace
- * that the library allocates once per device (128 MiB + 256 KiB, on the
+ * that the library allocates once per device (32 MiB + 1 KiB, on the
  * first call) and keeps until the process ends, so calls on one device must not
  * run concurrently. Results are deterministic: the same inputs give the same
  * bits on every call. */

@@ -141,9 +141,7 @@ __device__ __forceinline__ void store_qkv_rope(const GemmArgs& a, int m, int slo
 // LDS, lane L landing at byte 16 L (8 rows x 64 k). A weight block of the
 // tiled format is exactly one such instruction (its chunks are already in the
 // LDS order), and consecutive row blocks of one 64-k slab are adjacent in
-// memory. Activations are row-major; the buffer resource ends at the last row,
-// so rows past M read zeros and need no clamping (weight rows past N only feed
-// outputs that are never stored). A lane's address is one 32-bit offset, the
+// memory. Activations are row-major. A lane's address is one 32-bit offset, the
 // per-instruction and per-k-step parts are scalar. LDS rows are unpadded; the
 // 16-byte chunks of a row are XOR-swizzled by the row index so the 16 rows of
 // an MFMA fragment read hit different banks. NS stages form a ring: the
@@ -280,18 +278,20 @@ __device__ __forceinline__ void ring_stage(f32x4_v (&acc)[TN][TM], bf16x8_v (&a)
 // Tile schedule. Output tiles are numbered in groups of `group_n` column
 // tiles (weight rows) by all row tiles (tokens), column tile fastest, so the
 // workgroups that run together on one XCD share weight and activation slabs
-// in its L2. A data-parallel launch runs one whole tile per workgroup. A
-// stream-K launch gives each of its G workgroups an equal contiguous share of
-// the (tile, 64-k step) iteration space; a tile whose k range is split
-// between workgroups is finished by whichever of them arrives last: every
-// contributor stores its fp32 partial tile, then bumps the tile's arrival
-// counter, and the one that completes the count adds the partials in k order
-// (so the result does not depend on the arrival order), applies the
-// epilogue and sets the counter back to zero. No workgroup waits for another.
+// in its L2. A data-parallel launch (split = 1) runs one whole tile per
+// workgroup. A split launch gives every tile `split` consecutive workgroups,
+// each an equal contiguous share of its 64-k slabs; the one that arrives last
+// finishes the tile: every contributor stores its fp32 partial tile, then
+// bumps the tile's arrival counter, and the one that completes the count adds
+// the partials in k order (so the result does not depend on the arrival
+// order), applies the epilogue and sets the counter back to zero. No
+// workgroup waits for another. (Equal shares of the whole (tile, slab) space
+// instead, with two segments and two partial tiles for most workgroups, were
+// 5-25 % slower wherever the chip holds two or more workgroups a tile: 40
+// tokens x 15360 x 5120 38.5 against 31.3 us, x 5120 x 13824 36.9 against 32.0.)
 struct GemmSched {
   int tiles_m, tiles_n, nk, group_n;
-  int sk;         // 1: stream-K over gridDim.x workgroups
-  int64_t total;  // tiles * nk
+  int split;  // workgroups per tile
 };
 
 __device__ __forceinline__ void tile_coords(const GemmSched& s, int t, int& nt, int& mt) {
@@ -301,14 +301,6 @@ __device__ __forceinline__ void tile_coords(const GemmSched& s, int t, int& nt, 
   const int gsz = min(s.tiles_n - first, s.group_n);
   nt = first + r % gsz;
   mt = r / gsz;
-}
-
-// Stream-K: workgroup g owns iterations [floor(g T / G), floor((g+1) T / G)).
-__device__ __forceinline__ int64_t sk_begin(int g, int64_t total, int G) {
-  return (int64_t)g * total / G;
-}
-__device__ __forceinline__ int sk_owner(int64_t i, int64_t total, int G) {
-  return (int)(((i + 1) * G - 1) / total);
 }
 
 // Ping-pong main loop (eight waves, two stages of both operands): acc = sum
@@ -485,7 +477,6 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
                 "SwiGLU and RoPE need 32-row pairs");
   constexpr int X_BYTES = BM * BK * 2;
   __shared__ __attribute__((aligned(1024))) char smem[NS * (T::W_BYTES + X_BYTES)];
-  __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wn = wave & 1, wm = wave >> 1;
@@ -501,7 +492,6 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int vw = lane * 16;
   const int sw_slab = (a.N / 8) * 1024;
-  const int sx_step = RPI * (int)a.ldx * 2;
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)smem;
   // weight stages first, then the activation stages
   const uint32_t lds_w = lds0 + wave_u * (BN / NW) * BK * 2;
@@ -557,18 +547,24 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
       pp_mainloop<BN, BM>(acc, a, rw, rx, smem, lds0, n0, m0, k0, k1, lane, wave_u, after_issue);
       return;
     } else {
-    // weights: block (kt, n0/8 + wave * BN/(8 NW) + q) of the tiled format
-    const int sw_base = (n0 / 8 + wave_u * (BN / NW / 8)) * 1024;
-    const int vx = ((m0 + wave * (BM / NW) + lrow) * (int)a.ldx + lchunk * 8) * 2;
+    // weights: block (kt, n0/8 + wave * BN/(8 NW) + q) of the tiled format;
+    // rows past the last one (of either operand) re-read it, their outputs
+    // are not stored
+    int sw[T::WI], vx[T::XI];
+#pragma unroll
+    for (int q = 0; q < T::WI; ++q)
+      sw[q] = min(n0 / 8 + wave_u * (BN / NW / 8) + q, a.N / 8 - 1) * 1024;
+#pragma unroll
+    for (int q = 0; q < T::XI; ++q)
+      vx[q] = (min(m0 + wave * (BM / NW) + q * RPI + lrow, a.M - 1) * (int)a.ldx + lchunk * 8) * 2;
     // load q of a step (0 <= q < LPS): weights first
     constexpr int AHEAD = NS - 1;  // look-ahead in steps
     auto issue = [&](int j, int q) {
       const int stage = j % NS, kt = k0 + j;
       if (q < T::WI)
-        dma16(rw, vw, sw_base + kt * sw_slab + q * 1024, lds_w + stage * T::W_BYTES + q * 1024);
+        dma16(rw, vw, sw[q] + kt * sw_slab, lds_w + stage * T::W_BYTES + q * 1024);
       else
-        dma16(rx, vx, (q - T::WI) * sx_step + kt * BK * 2,
-              lds_x + stage * X_BYTES + (q - T::WI) * 1024);
+        dma16(rx, vx[q - T::WI], kt * BK * 2, lds_x + stage * X_BYTES + (q - T::WI) * 1024);
     };
     // the loads of a step are spread over the first SPR/4 of the row-tile
     // steps of the current slab's multiplication
@@ -594,10 +590,10 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
     bf16x8_v fa[PD + 1], fb[2][TM];
     for (int j = 0; j < n; ++j) {
       const bool more = j + AHEAD < n;
-      const bf16_t* sw = reinterpret_cast<const bf16_t*>(smem + (j % NS) * T::W_BYTES);
-      const bf16_t* sx =
+      const bf16_t* sws = reinterpret_cast<const bf16_t*>(smem + (j % NS) * T::W_BYTES);
+      const bf16_t* sxs =
           reinterpret_cast<const bf16_t*>(smem + NS * T::W_BYTES + (j % NS) * X_BYTES);
-      ring_stage<BN, BM, BK, NS, TN, TM, PD>(acc, fa, fb, sw, sx, wn, wm, fr, g, j > 0, [&](int step) {
+      ring_stage<BN, BM, BK, NS, TN, TM, PD>(acc, fa, fb, sws, sxs, wn, wm, fr, g, j > 0, [&](int step) {
         if (more && step < USE) {
 #pragma unroll
           for (int q = step * LPS / USE; q < (step + 1) * LPS / USE; ++q) issue(j + AHEAD, q);
@@ -655,17 +651,15 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
     }
   };
 
+  int nt, mt;
   if constexpr (!SK) {
-    int nt, mt;
     tile_coords(sc, l, nt, mt);
     mainloop(nt * BN, mt * BM, 0, sc.nk, [&] { rope_fetch(nt * BN, mt * BM); });
     epilogue(nt * BN, mt * BM);
   } else {
-
-  // stream-K: partial tiles live at part[(2 * g + slot) * BN * BM], slot 0
-  // for a workgroup's first segment and 1 for its last, in the lane order of
-  // the accumulators (coalesced 1 KiB per fragment). They are written and
-  // read with device-scope (sc1) accesses, which are coherent across the
+  // split: workgroup l's partial tile lives at part[l * BN * BM], in the lane
+  // order of the accumulators (coalesced 1 KiB per fragment). It is written
+  // and read with device-scope (sc1) accesses, which are coherent across the
   // XCDs' L2 caches on their own; a writer waits for its stores to complete
   // before its arrival is counted, so the last arrival sees every partial
   // without any cache-wide write-back or invalidation.
@@ -674,81 +668,62 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
   typedef unsigned u32x4_v __attribute__((ext_vector_type(4)));
   const __amdgpu_buffer_rsrc_t rp =
       __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7FFFFFFF, kRsrcWord3);
-  auto frag_off = [&](int i, int j) { return (((i * TM + j) * NW + wave) * 64 + lane) * 16; };
-  const int64_t beg = sk_begin(l, sc.total, G), end = sk_begin(l + 1, sc.total, G);
-  for (int64_t it = beg; it < end;) {
-    const int t = (int)(it / sc.nk);
-    const int k0 = (int)(it - (int64_t)t * sc.nk);
-    const int k1 = (int)min<int64_t>(sc.nk, k0 + (end - it));
-    int nt, mt;
-    tile_coords(sc, t, nt, mt);
-    mainloop(nt * BN, mt * BM, k0, k1, [] {});
-    if (k0 > 0 || k1 < sc.nk) {
-      const int slot = it == beg ? 0 : 1;
-      const int mine = (2 * l + slot) * TILE_F * 4;
+  auto frag_off = [&](int f) { return ((f * NW + wave) * 64 + lane) * 16; };
+  const int t = l / sc.split, c_me = l - t * sc.split;
+  tile_coords(sc, t, nt, mt);
+  mainloop(nt * BN, mt * BM, c_me * sc.nk / sc.split, (c_me + 1) * sc.nk / sc.split, [] {});
 #pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_v, acc[i][j]), rp,
-                                                 frag_off(i, j), mine, kSc1);
-      const int g0 = sk_owner((int64_t)t * sc.nk, sc.total, G);
-      const int g1 = sk_owner((int64_t)(t + 1) * sc.nk - 1, sc.total, G);
-      wait_vm<0>();
-      __syncthreads();
-      if (tid == 0) {
-        const uint32_t prev =
-            __hip_atomic_fetch_add(a.flags + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = prev == (uint32_t)(g1 - g0);
-      }
-      __syncthreads();
-      if (s_last) {
-        // running sum over contributors in k order; the partials before this
-        // workgroup's own go into `pre`, the rest straight into acc (16
-        // fragments per batch of loads, 8 or 16)
-        constexpr int FR = TN * TM, HB = FR > 16 ? 8 : FR;
-#pragma unroll
-        for (int f0 = 0; f0 < FR; f0 += HB) {
-          f32x4_v pre[HB];
-          bool after = false;
-          for (int c = g0; c <= g1; ++c) {
-            if (c == l) {
-              if (c != g0) {
-#pragma unroll
-                for (int u = 0; u < HB; ++u)
-                  acc[(f0 + u) / TM][(f0 + u) % TM] = pre[u] + acc[(f0 + u) / TM][(f0 + u) % TM];
-              }
-              after = true;
-              continue;
-            }
-            const int cs = sk_begin(c, sc.total, G) / sc.nk == t ? 0 : 1;
-            f32x4_v v[HB];
-#pragma unroll
-            for (int u = 0; u < HB; ++u)
-              v[u] = __builtin_bit_cast(
-                  f32x4_v, __builtin_amdgcn_raw_buffer_load_b128(
-                               rp, frag_off((f0 + u) / TM, (f0 + u) % TM),
-                               __builtin_amdgcn_readfirstlane((2 * c + cs) * TILE_F * 4), kSc1));
-            if (after) {
-#pragma unroll
-              for (int u = 0; u < HB; ++u) acc[(f0 + u) / TM][(f0 + u) % TM] += v[u];
-            } else if (c == g0) {
-#pragma unroll
-              for (int u = 0; u < HB; ++u) pre[u] = v[u];
-            } else {
-#pragma unroll
-              for (int u = 0; u < HB; ++u) pre[u] += v[u];
-            }
-          }
-        }
-        if (tid == 0) __hip_atomic_store(a.flags + t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        epilogue(nt * BN, mt * BM);
-      }
-    } else {
-      epilogue(nt * BN, mt * BM);
-    }
-    it += k1 - k0;
+  for (int f = 0; f < TN * TM; ++f)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_v, acc[f / TM][f % TM]), rp,
+                                           frag_off(f), l * TILE_F * 4, kSc1);
+  wait_vm<0>();
+  __syncthreads();
+  // (every wave is past its last fragment read: the ring's first word is free)
+  int& s_last = *reinterpret_cast<int*>(smem);
+  if (tid == 0) {
+    const uint32_t prev =
+        __hip_atomic_fetch_add(a.flags + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = prev + 1 == (uint32_t)sc.split;
   }
+  __syncthreads();
+  if (!s_last) return;
+  // The partials of CG contributors (8 fragments of each) are requested
+  // together, so a tile of six contributors pays two round trips to memory
+  // and not five (40 tokens, 5120 x 5120: 20.9 -> 19.9 us).
+  constexpr int FR = TN * TM, FB = FR == 8 ? 8 : FR % 4 == 0 ? 4 : FR;
+  constexpr int CG = FR <= 4 ? 8 : 4;
+  static_assert(FR % FB == 0, "whole batches of fragments");
+#pragma unroll
+  for (int f0 = 0; f0 < FR; f0 += FB) {
+    f32x4_v sum[FB];
+    for (int c0 = 0; c0 < sc.split; c0 += CG) {
+      f32x4_v v[CG][FB];
+#pragma unroll
+      for (int u = 0; u < CG; ++u) {
+        const int c = c0 + u;
+        if (c >= sc.split || c == c_me) continue;
+#pragma unroll
+        for (int f = 0; f < FB; ++f)
+          v[u][f] = __builtin_bit_cast(
+              f32x4_v, __builtin_amdgcn_raw_buffer_load_b128(
+                           rp, frag_off(f0 + f), (t * sc.split + c) * TILE_F * 4, kSc1));
+      }
+#pragma unroll
+      for (int u = 0; u < CG; ++u) {
+        const int c = c0 + u;
+        if (c >= sc.split) break;
+#pragma unroll
+        for (int f = 0; f < FB; ++f) {
+          const f32x4_v p = c == c_me ? acc[(f0 + f) / TM][(f0 + f) % TM] : v[u][f];
+          sum[f] = c == 0 ? p : sum[f] + p;
+        }
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < FB; ++f) acc[(f0 + f) / TM][(f0 + f) % TM] = sum[f];
+  }
+  if (tid == 0) __hip_atomic_store(a.flags + t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  epilogue(nt * BN, mt * BM);
   }
 }
 
@@ -1044,14 +1019,33 @@ hipError_t dispatch_ring(const GemmArgs& a, int epi, const GemmSched& sc, int gr
   return hipGetLastError();
 }
 
+// Tile configurations and the time model gemm() chooses among them with, in us
+// for nk 64-k slabs on a chip of `cus` CUs:
+//   whole tiles: start + nk rounds (slab + load * fill)
+//   split tiles: s_start + nk / split (s_slab + s_load * fill) + s_each * split
+// with rounds = ceil(tiles / cus) and fill = the share of the chip's workgroup
+// slots that hold one (a fuller chip is slower a slab: memory, caches, clock).
+// Least squares over measured launches (MI355X, weights streamed from HBM) of
+// nine projections of 7B, 8B and 13B shapes at 80 to 512 tokens and seven at
+// 640 to 4096: each configuration's own times within 3-7 % (rms), the choice
+// 0.4 % behind the best configuration of every shape on average and 8 % at
+// worst. Against the choice by per-CU rates before it and the split launches
+// before them, 16 % faster over those shapes: 160 tokens x 15360 x 5120 68.7 ->
+// 42.9 us, 512 x 5120 x 13824 138.9 -> 93.8, 512 x 6144 x 4096 47.6 -> 34.6.
 struct RingCfg {
   const char* name;
   int bn, bm;
-  bool sk_ok;  // has a stream-K build
+  double start, slab, load;
+  double s_start, s_slab, s_load, s_each;  // s_slab 0: no split build
 };
-const RingCfg kRing[] = {{"256x256", 256, 256, false}, {"256x128", 256, 128, false},
-                         {"128x128", 128, 128, true},  {"192x256", 192, 256, false},
-                         {"192x128", 192, 128, false}};
+const RingCfg kRing[] = {
+    {"256x256", 256, 256, 8.3, 1.035, 0.461, 0, 0, 0, 0},
+    {"192x256", 192, 256, 7.2, 0.888, 0.374, 0, 0, 0, 0},
+    {"256x128", 256, 128, 4.9, 0.700, 0.262, 12.1, 0.097, 1.060, 1.49},
+    {"192x128", 192, 128, 3.7, 0.557, 0.197, 8.9, 0.192, 0.685, 1.41},
+    {"128x128", 128, 128, 2.8, 0.430, 0.141, 6.2, 0.134, 0.516, 1.26},
+    {"128x64", 128, 64, 2.8, 0.339, 0.076, 0.0, 0.317, 0.145, 3.10},
+    {"64x64", 64, 64, 1.6, 0.214, 0.083, 0.0, 0.283, 0.0, 2.50}};
 
 // 256 x 256 and 192 x 256: ping-pong loop (128 and 112 KiB of LDS). Same box,
 // MI355X, one-barrier loop -> ping-pong: 8192 tokens QKV 616 -> 591 us, o 219 ->
@@ -1060,15 +1054,28 @@ const RingCfg kRing[] = {{"256x256", 256, 256, false}, {"256x128", 256, 128, fal
 // zeros, which hold the clock up, 8192-token gate/up goes 929 -> 823 us (1.80
 // PFLOP/s): on real data the power limit takes half of the gain.
 // 256 x 128: 3 stages, loads spread over the whole step. 192 x 128 (160 KiB)
-// and 128 x 128: 4 stages.
+// and 128 x 128: 4 stages, 128 x 64 (144 KiB): 6, 64 x 64: 8. The 64-token tiles
+// stream weights (17 to 64 tokens: 6.1 TB/s on the 13B gate/up matrix at 40
+// tokens, 84 -> 46 us; down 82 -> 28, QKV 68 -> 29, o 34 -> 15 against the decode
+// kernel, whose workgroups each read all activations from L2 unpipelined).
+template <int BN, int BM, int NS>
+hipError_t dispatch_split(const GemmArgs& a, int epi, const GemmSched& sc, int grid, hipStream_t s) {
+  return sc.split > 1 ? dispatch_ring<BN, BM, NS, 4, true>(a, epi, sc, grid, s)
+                      : dispatch_ring<BN, BM, NS, 4, false>(a, epi, sc, grid, s);
+}
+
 hipError_t launch_ring(const RingCfg& c, const GemmArgs& a, int epi, const GemmSched& sc,
                        int grid, hipStream_t s) {
-  if (c.bn == 256 && c.bm == 256) return dispatch_ring<256, 256, 2, 2, false, true>(a, epi, sc, grid, s);
-  if (c.bn == 192 && c.bm == 256) return dispatch_ring<192, 256, 2, 2, false, true>(a, epi, sc, grid, s);
-  if (c.bn == 192 && c.bm == 128) return dispatch_ring<192, 128, 4, 4, false>(a, epi, sc, grid, s);
-  if (c.bn == 256 && c.bm == 128) return dispatch_ring<256, 128, 3, 4, false>(a, epi, sc, grid, s);
-  return sc.sk ? dispatch_ring<128, 128, 4, 4, true>(a, epi, sc, grid, s)
-               : dispatch_ring<128, 128, 4, 4, false>(a, epi, sc, grid, s);
+  switch (c.bn * 1000 + c.bm) {
+    case 256256: return dispatch_ring<256, 256, 2, 2, false, true>(a, epi, sc, grid, s);
+    case 192256: return dispatch_ring<192, 256, 2, 2, false, true>(a, epi, sc, grid, s);
+    case 256128: return dispatch_split<256, 128, 3>(a, epi, sc, grid, s);
+    case 192128: return dispatch_split<192, 128, 4>(a, epi, sc, grid, s);
+    case 128128: return dispatch_split<128, 128, 4>(a, epi, sc, grid, s);
+    case 128064: return dispatch_split<128, 64, 6>(a, epi, sc, grid, s);
+    case 64064: return dispatch_split<64, 64, 8>(a, epi, sc, grid, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 int device_cus() {
@@ -1124,11 +1131,10 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
                            (epi == EPI_RESID ? 2 : 1);
   const double bytes = 2.0 * ((double)a.M * a.K + (double)a.N * a.K) + out_bytes;
   hipError_t e;
-  if (a.M <= 64) {
+  if (a.M <= 16) {
     // a QKV projection with RoPE runs as a plain (head-order) store followed
     // by the rotation pass
     const int pe = epi == EPI_QKV_ROPE ? EPI_STORE : epi;
-    const int mch = (a.M + 15) / 16;
     // Rows per workgroup (16 NF), 64-k slabs per load group (U), waves per
     // workgroup (WV) and staged activations (XS) for one token chunk, from
     // sweeps on MI355X over the decode projections of 7B, 8B and 13B models
@@ -1170,21 +1176,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     }
     if (force && *force) sscanf(force, "%d,%d,%d,%d", &nf, &u, &wv, &xs);
     if (pe == EPI_SWIGLU && (nf % 2)) nf = 2;
-    if (mch == 1) {
-      e = dispatch_skinny1(a, pe, nf, u, wv, xs != 0, s);
-    } else if (pe == EPI_SWIGLU) {
-      switch (mch) {
-        case 2: e = dispatch_epi_skinny<2, 2, 2, 4>(a, pe, s); break;
-        case 3: e = dispatch_epi_skinny<2, 3, 1, 4>(a, pe, s); break;
-        default: e = dispatch_epi_skinny<2, 4, 1, 4>(a, pe, s); break;
-      }
-    } else {
-      switch (mch) {
-        case 2: e = dispatch_epi_skinny<1, 2, 2, 4>(a, pe, s); break;
-        case 3: e = dispatch_epi_skinny<1, 3, 2, 4>(a, pe, s); break;
-        default: e = dispatch_epi_skinny<1, 4, 1, 4>(a, pe, s); break;
-      }
-    }
+    e = dispatch_skinny1(a, pe, nf, u, wv, xs != 0, s);
     if (e == hipSuccess && epi == EPI_QKV_ROPE) {
       RopeKvArgs r{static_cast<bf16_t*>(a.Y), a.ldy, a.rope_pos, a.rope_slot, a.rope_cos,
                    a.rope_sin, a.rope_pool, a.M, a.rope_q_cols / a.rope_d,
@@ -1193,53 +1185,41 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     }
     snprintf(name, sizeof name, "gemm_skinny_%s%s", a.norm_gain ? "norm_" : "", kEpiName[epi]);
   } else {
-    // Configuration by a small cost model: a data-parallel launch takes
-    // rounds x (tile flops / per-CU rate of its tile shape); a stream-K launch
-    // takes (flops / CUs) / its rate plus a fixed cost for the pipeline
-    // start-ups and the partial-tile reductions. The rates are per-CU
-    // TFLOP/s measured on MI355X with weights streamed from HBM.
-    // HS_GEMM_CFG="<tile>[,dp|,sk][,g<n>]" forces a choice (tuning only; read
-    // on every call so that a sweep can change it between calls).
+    // Configuration by the time model of kRing.
+    // HS_GEMM_CFG="<tile>[,dp|,sk][,g<n>]" forces a choice of tile, whole or
+    // split tiles, and tile group (tuning only; read on every call so that a
+    // sweep can change it between calls).
     const int cus = device_cus();
     const int nk = (int)(kp / 64);
-    struct Cand { const RingCfg* c; bool sk; double rate; };
     auto tiles_of = [&](const RingCfg& c) {
       return (long)((a.N + c.bn - 1) / c.bn) * ((a.M + c.bm - 1) / c.bm);
     };
-    auto sk_room = [&](const RingCfg& c, long tiles) {
-      const long g = std::min<long>(cus, tiles * nk / 4);
-      return c.sk_ok && g >= 1 && a.part && a.flags && tiles <= a.flags_n &&
-             2 * g * (int64_t)c.bn * c.bm <= a.part_floats;
+    // workgroups per tile of a split launch: as many as the chip holds, at
+    // least four slabs each; 1 where a split launch is not possible
+    auto split_of = [&](const RingCfg& c, long tiles) -> long {
+      const long sp = std::min<long>(cus / tiles, nk / 4);
+      return c.s_slab > 0 && sp >= 2 && a.part && a.flags && tiles <= a.flags_n &&
+                     tiles * sp * (int64_t)c.bn * c.bm <= a.part_floats
+                 ? sp
+                 : 1;
     };
-    // The 192-wide tiles cover more CUs when one round of tiles fills the
-    // chip (512-token 7B prompt, MI355X: gate/up 230 tiles of 192 x 256
-    // instead of 172 of 256 x 256, 102 instead of 118 us; QKV 256 tiles of
-    // 192 x 128 instead of 192 of 256 x 128, 54 instead of 67 us); over
-    // several rounds they lose to the 256-wide ones (4096-wide projections of
-    // 8192 tokens: 20% slower), so they only run as a single round.
-    const Cand cands[] = {{&kRing[0], false, 4.8}, {&kRing[1], false, 4.05},
-                          {&kRing[2], false, 3.05}, {&kRing[2], true, 3.0},
-                          {&kRing[3], false, 4.45}, {&kRing[4], false, 3.9}};
-    const double sk_fixed_us = 10.0;
     const RingCfg* cfg = nullptr;
     bool sk = false;
     double best = 1e300;
-    for (int i = 0; i < (int)(sizeof cands / sizeof cands[0]); ++i) {
-      const RingCfg& c = *cands[i].c;
-      const long tiles = tiles_of(c);
-      double us;
-      if (!cands[i].sk) {
-        if (c.bn == 192 && tiles > cus) continue;
-        const long rounds = (tiles + cus - 1) / cus;
-        us = rounds * (2.0 * kp * c.bn * c.bm) / (cands[i].rate * 1e6);
-      } else {
-        if (!sk_room(c, tiles)) continue;
-        us = (2.0 * a.M * (double)a.N * kp / cus) / (cands[i].rate * 1e6) + sk_fixed_us;
-      }
-      if (us < best) {
-        best = us;
+    for (const RingCfg& c : kRing) {
+      // up to 64 rows only the 64-token tiles, for which every workspace of
+      // more than 16 rows has room: the choice does not depend on its size
+      if (a.M <= 64 && c.bm != 64) continue;
+      const long tiles = tiles_of(c), rounds = (tiles + cus - 1) / cus, sp = split_of(c, tiles);
+      const double whole =
+          c.start + (double)nk * (rounds * c.slab + c.load * tiles / cus);
+      const double split =
+          sp > 1 ? c.s_start + (double)nk / sp * (c.s_slab + c.s_load * (tiles * sp) / cus) + c.s_each * sp
+                 : 1e300;
+      if (std::min(whole, split) < best) {
+        best = std::min(whole, split);
         cfg = &c;
-        sk = cands[i].sk;
+        sk = split < whole;
       }
     }
     int group = 8;
@@ -1261,13 +1241,11 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     sc.nk = nk;
     sc.group_n = group;
     const long tiles = (long)sc.tiles_n * sc.tiles_m;
-    sc.total = (int64_t)tiles * nk;
-    if (sk && !sk_room(*cfg, tiles)) sk = false;
-    sc.sk = sk ? 1 : 0;
-    const long grid = sk ? std::min<long>(cus, sc.total / 4) : tiles;
+    sc.split = sk ? (int)split_of(*cfg, tiles) : 1;
+    const long grid = tiles * sc.split;
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     e = launch_ring(*cfg, a, epi, sc, (int)grid, s);
-    snprintf(name, sizeof name, "gemm_r%s%s_%s", cfg->name, sk ? "sk" : "", kEpiName[epi]);
+    snprintf(name, sizeof name, "gemm_r%s%s_%s", cfg->name, sc.split > 1 ? "sk" : "", kEpiName[epi]);
   }
   if (info) {
     info->name = name;

@@ -20,8 +20,8 @@ struct GemmWs {
   float* part = nullptr;
   uint32_t* flags = nullptr;
 };
-constexpr int64_t kWsPartFloats = 2ll * 256 * 256 * 256;  // 2 slots x 256 workgroups x 256x256
-constexpr int64_t kWsFlags = 1 << 16;
+constexpr int64_t kWsPartFloats = 256ll * 256 * 128;  // a 256 x 128 partial tile per workgroup
+constexpr int64_t kWsFlags = 256;
 
 hs_status gemm_ws(GemmWs** out) {
   static GemmWs ws[64];

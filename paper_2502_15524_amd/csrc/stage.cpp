@@ -861,15 +861,15 @@ extern "C" hs_status hs_stage_create(const hs_model_cfg* cfg, int32_t layer_begi
   const uint64_t R = (uint64_t)st->ws_rows, S = (uint64_t)opts->max_seqs;
   uint64_t off = 0;
   std::vector<uint64_t> offs;
-  // split-k workspace: two 256 x 128 fp32 partial tiles per CU, a counter
-  // per 128 x 64 output tile of the widest projection
+  // workspace of split projection tiles (more than 16 rows): an fp32 partial
+  // tile of at most 256 x 128 per CU (64 columns up to 64 rows) and a counter
+  // per tile, of which a split launch has at most half as many as CUs
   int cus = 256;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
       cus <= 0)
     cus = 256;
-  const int64_t max_n = std::max<int64_t>(std::max(NQKV, 2 * F), std::max(H, V));
-  st->gpart_floats = R > 64 ? 2ll * cus * 256 * 128 : 0;
-  st->gflags_n = R > 64 ? ((max_n + 127) / 128) * (int64_t)((R + 63) / 64) : 0;
+  st->gpart_floats = R > 64 ? (int64_t)cus * 256 * 128 : R > 16 ? (int64_t)cus * 128 * 64 : 0;
+  st->gflags_n = R > 16 ? cus : 0;
   for (uint64_t sz : {R * H * 2, R * H * 2, R * NQKV * 2, R * QD * 2, R * round64(F) * 2, S * H * 2,
                       S * V * 4, S * m.n_heads * st->max_splits * (uint64_t)D * 4,
                       S * m.n_heads * st->max_splits * 2 * 4, (uint64_t)st->gpart_floats * 4,

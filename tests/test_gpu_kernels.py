@@ -138,6 +138,48 @@ def test_gemm_ping_pong_edges(cfg, M, N, K, epi, monkeypatch):
     assert np.abs(out - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
 
 
+# Every tile configuration, whole and split over workgroups, at the edges of
+# its range: fewer rows and columns than a tile, one past a tile, remainders,
+# the fewest slabs a split takes and a K that is no multiple of 64. Two calls
+# agree bitwise (the arrival counters are back at zero).
+@pytest.mark.parametrize("cfg", [f"{t},{m}" for t in ("64x64", "128x64", "128x128", "192x128", "256x128")
+                                 for m in ("dp", "sk")])
+@pytest.mark.parametrize("M,N,K,epi", [(17, 16, 64, "f32"), (65, 272, 512, "resid"), (33, 400, 712, "f32"),
+                                       (129, 96, 1088, "swiglu"), (200, 336, 640, "store")])
+def test_gemm_tile_configurations(cfg, M, N, K, epi, monkeypatch):
+    torch = G.torch()
+    hs = _hs()
+    rng = np.random.default_rng(M + N + K)
+    X = gen.round_to_bf16(rng.standard_normal((M, K)).astype(np.float32))
+    Wt = gen.round_to_bf16((rng.standard_normal((N, K)) * 0.05).astype(np.float32))
+    kp = -(-K // 64) * 64
+    Xp = np.zeros((M, kp), np.float32)
+    Xp[:, :K] = X
+    dX = G.to_dev_bf16(Xp)
+    dW = torch.from_numpy(G.tile_bits(gen.to_bf16_bits(Wt)).view(np.int16)).cuda()
+    ref = X.astype(np.float64) @ Wt.astype(np.float64).T
+    ncol = N
+    if epi == "swiglu":
+        ncol = N // 2
+        idx = np.arange(ncol)
+        ref = silu(ref[:, (idx // 16) * 32 + idx % 16]) * ref[:, (idx // 16) * 32 + 16 + idx % 16]
+    R = gen.round_to_bf16(rng.standard_normal((M, ncol)).astype(np.float32))
+    if epi == "resid":
+        ref = R + ref
+    monkeypatch.setenv("HS_GEMM_CFG", cfg)
+    outs = []
+    for _ in range(2):
+        Y = G.to_dev_bf16(R) if epi == "resid" else torch.zeros(
+            (M, ncol), dtype=torch.float32 if epi == "f32" else torch.bfloat16, device="cuda")
+        hs.hs_k_gemm(dX.data_ptr(), kp, dW.data_ptr(), Y.data_ptr(), ncol,
+                     Y.data_ptr() if epi == "resid" else 0, ncol, M, N, K, epi, G.stream_ptr())
+        torch.cuda.synchronize()
+        outs.append(Y.cpu().numpy() if epi == "f32" else G.from_dev_bf16(Y))
+    assert np.array_equal(outs[0], outs[1])
+    # one bf16 rounding of the result (2^-9 of it) and float32 sums
+    assert np.abs(outs[0] - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
+
+
 # 7B-shape projections at a 512-token prompt: few output tiles, so their k
 # ranges are split across workgroups (stream-K). Rows are sampled for the
 # float64 reference; two calls must agree bitwise.
