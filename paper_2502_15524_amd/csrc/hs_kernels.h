@@ -84,12 +84,13 @@ struct AttnPrefillArgs {
   const int32_t* cu;              // [n_seqs + 1] token offsets
   const int32_t* tiles;           // [n_tiles][2] (sequence, first query row, multiple of q_tile)
   int n_tiles, n_heads, n_kv_heads, D;
-  int waves, q_tile;              // 4 or 8 waves; q_tile = 16 * waves queries per workgroup
+  int waves, q_tile;              // 4 (narrow) or 8 (wide); q_tile = 16 * waves queries per workgroup
   double flops;                   // unmasked-pair flops, for reporting
 };
 hipError_t attn_prefill(const AttnPrefillArgs& a, hipStream_t s, LaunchInfo* info);
-// Waves per prefill-attention workgroup for a problem with `tiles_of_128`
-// 128-query tiles (summed over sequences) and n_heads heads.
+// Form of the prefill attention for a problem with `tiles_of_128` 128-query
+// tiles (summed over sequences) and n_heads heads: 4 = 64-query tiles, 8 =
+// 128-query tiles.
 int attn_prefill_waves(int64_t tiles_of_128, int n_heads);
 
 constexpr int kDecodeSplit = 128;  // tokens per split of the decode attention

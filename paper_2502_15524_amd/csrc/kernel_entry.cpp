@@ -110,11 +110,15 @@ extern "C" hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t
       tiles128 += (len + 127) / 128;
     }
     const int waves = attn_prefill_waves(tiles128, n_heads);
+    // longest rows first, as the stage orders them
+    std::vector<std::pair<int32_t, int32_t>> order;
     for (int i = 0; i < n; ++i)
-      for (int q = 0; q < cu[i + 1] - cu[i]; q += 16 * waves) {
-        tiles.push_back(i);
-        tiles.push_back(q);
-      }
+      for (int q = 0; q < cu[i + 1] - cu[i]; q += 16 * waves) order.emplace_back(-q, i);
+    std::sort(order.begin(), order.end());
+    for (const auto& t : order) {
+      tiles.push_back(t.second);
+      tiles.push_back(-t.first);
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
     int32_t* d = nullptr;
     const size_t nb = (size_t)(n + 1 + tiles.size()) * 4;

@@ -225,7 +225,12 @@ def test_gemm_split_k_shapes(N, K, epi):
     # workgroup counts 512 and 380 (D = 128), 320 and 276 (D = 64), so both
     # multiples of 8 and others
     ([1024], 32, 8, 128), ([1000, 150], 20, 5, 128), ([900, 300], 16, 4, 64),
-    ([1000, 400], 12, 6, 64)])
+    ([1000, 400], 12, 6, 64),
+    # 128-query tiles at their edges: sequence ends around 32-query waves,
+    # 64-key blocks and tiles; heads in eighths (1, 3, 4 an XCD) and not
+    ([1, 31, 33, 63, 64, 65, 127, 128, 129, 191, 257], 32, 8, 128),
+    ([1, 95, 97, 128, 129, 320], 24, 24, 64), ([130, 5, 449], 36, 9, 128),
+    ([300, 257, 64, 1, 640], 8, 2, 64)])
 def test_attn_prefill(lens, nh, nkv, d):
     torch = G.torch()
     hs = _hs()
