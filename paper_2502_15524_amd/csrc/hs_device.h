@@ -70,6 +70,19 @@ __device__ __forceinline__ float silu_f(float g) {
   return g / (1.0f + fast_exp2(-g * 1.4426950408889634f));
 }
 
+// One thread's 16 bytes of a pull from pinned host memory (units i of n16): the
+// loads are system-coherent (sc0 sc1), so they see what the host wrote before
+// the launch, never a cached copy of an earlier call's values.
+__device__ __forceinline__ void pull16(const int32_t* host, int32_t* dev, int n16, int i) {
+  if (i >= n16) return;
+  typedef unsigned u32x4_v __attribute__((ext_vector_type(4)));
+  constexpr int kSystem = 1 | 16;  // sc0 | sc1
+  const __amdgpu_buffer_rsrc_t r =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(host), 0, n16 * 16, 0x00020000);
+  const u32x4_v v = __builtin_amdgcn_raw_buffer_load_b128(r, i * 16, 0, kSystem);
+  *reinterpret_cast<u32x4_v*>(dev + (int64_t)i * 4) = v;
+}
+
 // Rotate-half RoPE of one pair: x1 at index i of a head's first half, x2 at
 // i + D/2, angle with cosine c and sine s. Every kernel that rotates uses
 // these two (with explicit fused multiply-adds), so they all round alike.

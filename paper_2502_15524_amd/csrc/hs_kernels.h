@@ -10,6 +10,19 @@ namespace hs {
 
 typedef uint16_t bf16_t;
 
+// Per-call metadata pulled from pinned host memory into device memory (both
+// 16-byte aligned, n16 units of 16 bytes) by extra workgroups of a call's first
+// kernel, which does not read it itself.
+struct MetaPull {
+  const int32_t* host = nullptr;
+  int32_t* dev = nullptr;
+  int n16 = 0;
+  // workgroups of `threads` threads it takes
+  __host__ __device__ int blocks(int threads) const { return (n16 + threads - 1) / threads; }
+};
+
+bool pull_ok(const MetaPull& p);  // alignment and size
+
 // Epilogues of Y[m][n] = sum_k X[m][k] * W[n][k] (fp32 accumulation).
 enum Epi : int {
   EPI_STORE = 0,   // Y = bf16(acc)
@@ -49,6 +62,7 @@ struct GemmArgs {
   const float* rope_cos = nullptr; const float* rope_sin = nullptr;
   int rope_max_pos = 0;
   bf16_t* rope_pool = nullptr;
+  MetaPull pull;  // M <= 16 only
 };
 
 // Describes what was launched (for timing).
@@ -61,12 +75,12 @@ struct LaunchInfo {
 hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info);
 
 hipError_t embed(const int32_t* tok, const bf16_t* E, int vocab, int hidden, int n_tok,
-                 bf16_t* out, hipStream_t s, LaunchInfo* info);
+                 bf16_t* out, hipStream_t s, LaunchInfo* info, const MetaPull& pull = MetaPull());
 
 // out[r] = rmsnorm(x[rows ? rows[r] : r]) * g
 hipError_t rmsnorm(const bf16_t* x, int64_t ldx, const int32_t* rows, int n_rows, int hidden,
                    const bf16_t* g, float eps, bf16_t* out, int64_t ldo, hipStream_t s,
-                   LaunchInfo* info);
+                   LaunchInfo* info, const MetaPull& pull = MetaPull());
 
 struct RopeKvArgs {
   bf16_t* qkv; int64_t ld;       // [T][ld]: q heads, k heads, v heads
@@ -126,8 +140,8 @@ hipError_t argmax_rows(const float* logits, int n_rows, int n_cols, int32_t* par
 
 // Copy `n` int32 values (n % 4 == 0, both pointers 16-byte aligned) from
 // pinned host memory to device memory with system-coherent loads, and in the
-// same launch `n2` more from host2 to dev2 (same rules; n2 = 0: none): the
-// per-call metadata and copy descriptors of a stage, pulled by a kernel.
+// same launch `n2` more from host2 to dev2 (same rules; n2 = 0: none): the copy
+// descriptors and the blob header of a KV copy, pulled by a kernel.
 hipError_t meta_pull(const int32_t* host, int32_t* dev, int64_t n, hipStream_t s,
                      const int32_t* host2 = nullptr, int32_t* dev2 = nullptr, int64_t n2 = 0);
 

@@ -16,9 +16,9 @@
 //  * gemm_ring   - prefill: BN x BM x 64 tiles copied straight into an LDS ring
 //                  of NS stages, 8 waves, 16x16x32 bf16 MFMA, XCD-aware order;
 //                  256-token tiles run a ping-pong main loop.
-//  * gemm_skinny - decode (M <= 64 tokens): HBM-bound weight streaming, 2,
-//                  4 or 8 waves split K inside a workgroup, reduced through
-//                  LDS in a fixed order (deterministic).
+//  * gemm_skinny - decode (M <= 16 tokens): HBM-bound weight streaming, 2 to
+//                  16 waves split K inside a workgroup, reduced through LDS in
+//                  a fixed order (deterministic).
 #include "hs_device.h"
 #include "hs_kernels.h"
 
@@ -729,7 +729,7 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 
 // ------------------------------------------------------------ skinny (decode)
 //
-// A workgroup owns 16 * NF weight rows and all M <= 64 tokens; its WV waves
+// A workgroup owns 16 * NF weight rows and all M <= 16 tokens; its WV waves
 // split the 64-column slabs of K. For one slab, the 2 NF row blocks of the
 // workgroup are adjacent 1 KiB blocks. Each is read by one wave-wide 16-byte
 // load with lane L taking bytes [16 L, 16 L + 16) (a whole block per
@@ -739,19 +739,23 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 // the ks-th 32-k MFMA. The buffer keeps the block's XOR-swizzled chunk order,
 // so the fragment reads are free of bank conflicts. (Loading the fragments
 // straight from global memory makes every instruction touch half of each of
-// 16 rows; the whole-block loads stream 10-30% faster on MI355X.) The loads
-// of the next slab group are issued before the current one is multiplied.
-//
-// The activations (the B operand, tokens on the MFMA columns) are loaded in
+// 16 rows; the whole-block loads stream 10-30% faster on MI355X.) The
+// activations (the B operand, tokens on the MFMA columns) are loaded in
 // fragment order, lane (fr, g) taking chunk 4 ks + g of token fr: 64 bytes of
 // each of 16 rows per instruction. With XS they take the weights' route
-// instead: instruction h of a 16-token chunk reads whole 128-byte rows of
-// tokens 8h .. 8h + 7 (lane L: token 8h + L/8, chunk (L % 8) ^ (L / 8)) and
-// stores them to position 64 h + L of the wave's activation buffer, which
-// then has the layout of a weight tile's image and is read like one. The
-// MFMA operands are the same either way; staging pays off once many tokens
-// share the call (8B-shape o and down projections at 16 tokens, MI355X:
-// 12.3 -> 9.7 and 26.5 -> 23.5 us) and costs about 0.5 us at one token.
+// instead: instruction h reads whole 128-byte rows of tokens 8h .. 8h + 7 into
+// an image laid out and read like a weight tile's. The MFMA operands are the
+// same; whole rows pay off from 8 tokens on, where the activations the previous
+// kernel wrote come from beyond the XCD's L2 (8B layer at 16 tokens, in the
+// decode step: o and down 36.6 -> 31.6 us together).
+//
+// A slab's loads are issued as its registers come free, weights before
+// activations, so no wait for one slab covers a later one's loads. (Loads
+// complete in order: with the activations of slab s requested after the weights
+// of slab s + 1, the wait for them drained those as well. 7B, 8B and 13B shapes
+// at 1 to 16 tokens, MI355X, before -> after: QKV 19.8 -> 18.2, 12.9 -> 11.0 and
+// 27.1 -> 25.5 us, gate/up 29.9 -> 29.4, 39.2 -> 36.3 and 45.4 -> 42.3, LM head with
+// its norm 178 -> 153, 13B down 26.2 -> 23.8.)
 
 // With NORM, X is the un-normalised residual stream and the GEMM applies the
 // RMSNorm of its rows itself: each loaded activation chunk is multiplied by
@@ -759,192 +763,165 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 // of the raw values are summed along the way, and the epilogue scales each
 // token's outputs by 1 / sqrt(mean square + eps). Used for decode, where the
 // separate norm kernel would cost a launch per projection.
-template <int NF, int MCH, int U, int EPI, bool NORM, int WV, bool XS>
+template <int NF, int EPI, bool NORM, int WV, bool XS>
 __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
   static_assert(EPI != EPI_SWIGLU || (NF % 2) == 0, "SwiGLU needs gate/up tile pairs");
   // the norm's sums of squares follow the fragment-order loads; keeping one
   // order for every batch size keeps a token's result independent of M
   static_assert(!(NORM && XS), "staged activations are built without the fused norm");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * 16 * NF;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // a call's first kernel also pulls its metadata, in its first workgroups
+  const int pb = a.pull.blocks(64 * WV);
+  if ((int)blockIdx.x < pb)
+    return pull16(a.pull.host, a.pull.dev, a.pull.n16, blockIdx.x * 64 * WV + threadIdx.x);
+  const int n0 = ((int)blockIdx.x - pb) * 16 * NF;
   const int kp = (a.K + 63) & ~63;
   const int nslab = kp / 64;
   const int sq = (nslab + WV - 1) / WV;  // slabs per wave
   const int sb = wave * sq, se = min(nslab, sb + sq);
   const int fr = lane & 15, g = lane >> 4;
-  const int64_t slab_bytes = (int64_t)(a.N / 8) * 1024;
+  const int slab_bytes = (a.N / 8) * 1024;
+  // Loads past a wave's last slab, of row tiles past N and of tokens past M
+  // get an offset past the end of their buffer: they read zeros and touch no
+  // memory, and no load is behind a branch (the waits stay exact).
+  constexpr int kPast = (int)0x80000000u;
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(a.W), 0, (int)((int64_t)a.N * kp * 2), kRsrcWord3);
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(a.X), 0, (int)((int64_t)a.M * a.ldx * 2), kRsrcWord3);
+  const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(NORM ? a.norm_gain : a.X), 0, a.K * 2, kRsrcWord3);
   // instruction (f, h) of a slab reads row block n0 / 8 + 2 f + h (N % 16 == 0,
   // so a 16-row tile is either wholly inside the matrix or wholly outside)
-  const char* wbase = reinterpret_cast<const char*>(a.W) + (int64_t)(n0 / 8) * 1024 + lane * 16;
-  bool wok[NF];
+  const int wbase = (n0 / 8) * 1024 + lane * 16;
+  int wpast[NF];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) wok[f] = n0 + 16 * f < a.N;
+  for (int f = 0; f < NF; ++f) wpast[f] = n0 + 16 * f < a.N ? 0 : kPast;
   const int r8 = fr % 8;
   // 16-byte position of lane (fr, g)'s row inside the 2 KiB image of a 16-row tile
   const int fpos = (fr / 8) * 64 + r8 * 8;
-  // activation rows. XS: load i = 2 c + h (instruction h of token chunk c)
-  // reads token 8 i + L / 8, at 16-byte chunk (L % 8) ^ (L / 8) of each slab;
-  // otherwise load c reads token 16 c + fr (its chunk offset added per load)
-  constexpr int XH = XS ? 2 : 1;
-  const int xr = lane >> 3, xc = (lane & 7) ^ (lane >> 3);
-  const bf16_t* xrow[MCH * XH];
+  // activations. XS: instruction h reads token 8 h + L / 8, at 16-byte chunk
+  // (L % 8) ^ (L / 8) of each slab; otherwise instruction ks reads chunk
+  // 4 ks + g of token fr
+  int xoff[2];
 #pragma unroll
-  for (int i = 0; i < MCH * XH; ++i) {
-    const int m = XS ? 8 * i + xr : 16 * i + fr;
-    xrow[i] = (m < a.M) ? a.X + (int64_t)m * a.ldx + (XS ? xc * 8 : 0) : nullptr;
+  for (int i = 0; i < 2; ++i) {
+    const int m = XS ? 8 * i + (lane >> 3) : fr;
+    const int chunk = XS ? (lane & 7) ^ (lane >> 3) : 4 * i + g;
+    xoff[i] = m < a.M ? m * (int)a.ldx * 2 + chunk * 16 : kPast;
   }
-  // per wave and slab: the weight tiles' images, then with XS the activation
-  // chunks' images (16-byte units)
-  __shared__ pack8 wlds[WV][U][(NF + (XS ? MCH : 0)) * 128];
+  // per wave: the weight tiles' images of a slab, then with XS the
+  // activations' (16-byte units); after the last slab, the wave's partial sums
+  __shared__ pack8 wlds[WV][(NF + (XS ? 1 : 0)) * 128];
 
-  f32x4_v acc[NF][MCH];
-  float ssq[MCH];
+  f32x4_v acc[NF];
+  float ssq = 0.f;
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
-#pragma unroll
-    for (int c = 0; c < MCH; ++c) acc[f][c] = f32x4_v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < MCH; ++c) ssq[c] = 0.f;
+  for (int f = 0; f < NF; ++f) acc[f] = f32x4_v{0.f, 0.f, 0.f, 0.f};
 
-  pack8 wv[U][NF][2];
-  auto load_w = [&](int s0) {
+  typedef unsigned u32x4_v __attribute__((ext_vector_type(4)));
+  constexpr int kNt = 2;  // cache policy: streamed once per call
+  u32x4_v wv[NF][2], xv[2], gv[2];
+  auto load_x = [&](int sl) {
+    // uniform, and or-ed in: a select here becomes a branch
+    const int past = sl < se ? 0 : kPast;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int sl = s0 + u;
-      const bool ok = sl < se;
-#pragma unroll
-      for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          wv[u][f][h] = (ok && wok[f]) ? ld16_nt(wbase + sl * slab_bytes + (2 * f + h) * 1024)
-                                       : zero8();
+    for (int ks = 0; ks < 2; ++ks) {
+      xv[ks] = __builtin_amdgcn_raw_buffer_load_b128(rx, (xoff[ks] + sl * 128) | past, 0, 0);
+      if constexpr (NORM)
+        gv[ks] = __builtin_amdgcn_raw_buffer_load_b128(rg, (sl * 128 + (ks * 4 + g) * 16) | past, 0, 0);
     }
   };
-  if (sb < se) load_w(sb);
-  for (int s0 = sb; s0 < se; s0 += U) {
-    // this wave's buffer: the previous group's fragment reads were issued
+  auto load_w = [&](int sl) {
+    const int past = sl < se ? 0 : kPast;
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        wv[f][h] = __builtin_amdgcn_raw_buffer_load_b128(
+            rw, ((wbase + sl * slab_bytes) | past | wpast[f]) + (2 * f + h) * 1024, 0, kNt);
+  };
+  load_w(sb);
+  load_x(sb);
+  for (int sl = sb; sl < se; ++sl) {
+    // this wave's buffer: the previous slab's fragment reads were issued
     // before these stores, and one wave's LDS operations run in order
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
-      for (int f = 0; f < NF; ++f)
+      for (int h = 0; h < 2; ++h)
+        wlds[wave][(2 * f + h) * 64 + lane] = __builtin_bit_cast(pack8, wv[f][h]);
+    load_w(sl + 1);
+    pack8 xc[2], gc[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) wlds[wave][u][(2 * f + h) * 64 + lane] = wv[u][f][h];
-    if (s0 + U < se) load_w(s0 + U);
-    // activations: XS, whole rows (stored below); else fragment order, xv[c][u][ks]
-    pack8 xv[MCH][U][2], gv[U][2];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int sl = s0 + u;
-      const bool ok = sl < se;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const int chunk = ks * 4 + g;
-#pragma unroll
-        for (int c = 0; c < MCH; ++c) {
-          if constexpr (XS)
-            xv[c][u][ks] = (ok && xrow[2 * c + ks]) ? ld16(xrow[2 * c + ks] + sl * 64) : zero8();
-          else
-            xv[c][u][ks] = (ok && xrow[c]) ? ld16(xrow[c] + sl * 64 + chunk * 8) : zero8();
-        }
-        if constexpr (NORM) gv[u][ks] = ok ? ld16(a.norm_gain + sl * 64 + chunk * 8) : zero8();
-      }
+    for (int ks = 0; ks < 2; ++ks) {
+      xc[ks] = __builtin_bit_cast(pack8, xv[ks]);
+      if constexpr (XS) wlds[wave][NF * 128 + ks * 64 + lane] = xc[ks];
+      if constexpr (NORM) gc[ks] = __builtin_bit_cast(pack8, gv[ks]);
     }
+    load_x(sl + 1);
     if constexpr (NORM) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+      for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int c = 0; c < MCH; ++c) {
-            pack8& x = xv[c][u][ks];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float x0 = lo_bf(x.w[e]), x1 = hi_bf(x.w[e]);
-              ssq[c] += x0 * x0 + x1 * x1;
-              x.w[e] = pack2bf(x0 * lo_bf(gv[u][ks].w[e]), x1 * hi_bf(gv[u][ks].w[e]));
-            }
-          }
-    }
-    if constexpr (XS) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int c = 0; c < MCH; ++c)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) wlds[wave][u][NF * 128 + (2 * c + h) * 64 + lane] = xv[c][u][h];
+        for (int e = 0; e < 4; ++e) {
+          const float x0 = lo_bf(xc[ks].w[e]), x1 = hi_bf(xc[ks].w[e]);
+          ssq += x0 * x0 + x1 * x1;
+          xc[ks].w[e] = pack2bf(x0 * lo_bf(gc[ks].w[e]), x1 * hi_bf(gc[ks].w[e]));
+        }
     }
     asm volatile("" ::: "memory");  // keep the fragment reads after the stores
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int ks = 0; ks < 2; ++ks) {
+      if constexpr (XS)  // the fragments from the staged image (read like a weight tile's)
+        xc[ks] = wlds[wave][NF * 128 + fpos + ((ks * 4 + g) ^ r8)];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        if constexpr (XS) {  // the fragments from the staged image (read like a weight tile's)
-#pragma unroll
-          for (int c = 0; c < MCH; ++c)
-            xv[c][u][ks] = wlds[wave][u][(NF + c) * 128 + fpos + ((ks * 4 + g) ^ r8)];
-        }
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          const pack8 w = wlds[wave][u][f * 128 + fpos + ((ks * 4 + g) ^ r8)];
-#pragma unroll
-          for (int c = 0; c < MCH; ++c)
-            acc[f][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                as_bf16x8(w), as_bf16x8(xv[c][u][ks]), acc[f][c], 0, 0, 0);
-        }
+      for (int f = 0; f < NF; ++f) {
+        const pack8 w = wlds[wave][f * 128 + fpos + ((ks * 4 + g) ^ r8)];
+        acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w), as_bf16x8(xc[ks]), acc[f],
+                                                         0, 0, 0);
       }
+    }
     asm volatile("" ::: "memory");  // and the next stores after these reads
   }
 
-  __shared__ f32x4_v red[WV - 1][NF][MCH][64];
-  __shared__ float red_ss[WV][MCH][16];
+  // partial sums added in wave order; with SwiGLU wave p finishes the gate/up
+  // pair p of the workgroup, else row tile p (by one wave alone the reads of
+  // 15 partials of three tiles spilled 76 registers)
+  constexpr int PAIR = EPI == EPI_SWIGLU ? 2 : 1;
+  // (each wave's partials over its own, consumed, tile images: the LDS of a
+  // 128256-wide LM head's workgroup stays 32 KiB and its 1002 workgroups fit
+  // the chip in one round; with 48 KiB it took 175 us instead of 155)
+  const auto red = [&](int w, int f) { return reinterpret_cast<f32x4_v*>(wlds[w]) + f * 64 + lane; };
+  __shared__ float red_ss[WV][16];
   if constexpr (NORM) {
     // the 4 k-groups of a token (lanes fr, fr+16, fr+32, fr+48), then waves
-#pragma unroll
-    for (int c = 0; c < MCH; ++c) {
-      ssq[c] += __shfl_xor(ssq[c], 16, 64);
-      ssq[c] += __shfl_xor(ssq[c], 32, 64);
-      if (g == 0) red_ss[wave][c][fr] = ssq[c];
-    }
+    ssq += __shfl_xor(ssq, 16, 64);
+    ssq += __shfl_xor(ssq, 32, 64);
+    if (g == 0) red_ss[wave][fr] = ssq;
   }
-  if (wave > 0) {
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-      for (int c = 0; c < MCH; ++c) red[wave - 1][f][c][lane] = acc[f][c];
-  }
+  for (int f = 0; f < NF; ++f) *red(wave, f) = acc[f];
   __syncthreads();
-  if (wave != 0) return;
+  const int fq = g * 4;
+  for (int p = wave; p < NF / PAIR; p += WV) {
+    f32x4_v o[PAIR];
 #pragma unroll
-  for (int w = 0; w < WV - 1; ++w)
+    for (int i = 0; i < PAIR; ++i) {
+      o[i] = *red(0, p * PAIR + i);
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+      for (int w = 1; w < WV; ++w) o[i] += *red(w, p * PAIR + i);
+    }
+    if constexpr (NORM) {
+      float tot = red_ss[0][fr];
 #pragma unroll
-      for (int c = 0; c < MCH; ++c) acc[f][c] += red[w][f][c][lane];
-  if constexpr (NORM) {
-#pragma unroll
-    for (int c = 0; c < MCH; ++c) {
-      float tot = red_ss[0][c][fr];
-#pragma unroll
-      for (int w = 1; w < WV; ++w) tot += red_ss[w][c][fr];
+      for (int w = 1; w < WV; ++w) tot += red_ss[w][fr];
       const float inv = 1.0f / sqrtf(tot / (float)a.K + a.norm_eps);
 #pragma unroll
-      for (int f = 0; f < NF; ++f) acc[f][c] *= inv;
+      for (int i = 0; i < PAIR; ++i) o[i] *= inv;
     }
-  }
-
-  const int fq = g * 4;
-#pragma unroll
-  for (int c = 0; c < MCH; ++c) {
-    const int m = 16 * c + fr;
-    if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-      for (int f = 0; f < NF; f += 2)
-        store_swiglu(a, m, (n0 + 16 * f) / 2 + fq, acc[f][c], acc[f + 1][c]);
-    } else {
-#pragma unroll
-      for (int f = 0; f < NF; ++f) store4<EPI>(a, m, n0 + 16 * f + fq, acc[f][c]);
-    }
+    if constexpr (EPI == EPI_SWIGLU) store_swiglu(a, fr, n0 / 2 + 16 * p + fq, o[0], o[1]);
+    else store4<EPI>(a, fr, n0 + 16 * p + fq, o[0]);
   }
 }
 
@@ -952,55 +929,51 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
 
 namespace {
 
-template <int NF, int MCH, int U, int WV, bool XS, bool NORM>
+template <int NF, int WV, bool NORM, bool XS>
 hipError_t dispatch_skinny_norm(const GemmArgs& a, int epi, hipStream_t s) {
-  const int grid = (a.N + 16 * NF - 1) / (16 * NF);
+  const int grid = (a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV);
   const dim3 blk(64 * WV);
   switch (epi) {
     case EPI_STORE:
-      hipLaunchKernelGGL((gemm_skinny<NF, MCH, U, EPI_STORE, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+      hipLaunchKernelGGL((gemm_skinny<NF, EPI_STORE, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
       break;
     case EPI_RESID:
-      hipLaunchKernelGGL((gemm_skinny<NF, MCH, U, EPI_RESID, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+      hipLaunchKernelGGL((gemm_skinny<NF, EPI_RESID, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
       break;
     case EPI_SWIGLU:
       if constexpr (NF % 2 == 0) {
-        hipLaunchKernelGGL((gemm_skinny<NF, MCH, U, EPI_SWIGLU, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+        hipLaunchKernelGGL((gemm_skinny<NF, EPI_SWIGLU, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
         break;
       } else {
         return hipErrorInvalidValue;
       }
     case EPI_F32:
-      hipLaunchKernelGGL((gemm_skinny<NF, MCH, U, EPI_F32, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+      hipLaunchKernelGGL((gemm_skinny<NF, EPI_F32, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
       break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <int NF, int MCH, int U, int WV, bool XS = false>
+// The skinny variants, as (rows per workgroup / 16, waves per workgroup,
+// staged activations): the ones the selection in gemm() takes.
+#define HS_SKINNY_BUILDS(X)                                                    \
+  X(2, 8, false) X(2, 4, false) X(4, 4, false) X(2, 2, false) X(4, 2, false) \
+  X(8, 2, false) X(1, 16, false) X(3, 16, false) X(1, 16, true) X(2, 8, true)
+
+template <int NF, int WV, bool XS>
 hipError_t dispatch_epi_skinny(const GemmArgs& a, int epi, hipStream_t s) {
   if (a.norm_gain) {
-    // the fused norm is only built for one 16-token chunk (decode batches)
-    if constexpr (MCH == 1 && !XS) return dispatch_skinny_norm<NF, 1, U, WV, false, true>(a, epi, s);
+    if constexpr (!XS) return dispatch_skinny_norm<NF, WV, true, false>(a, epi, s);
     else return hipErrorInvalidValue;
   }
-  return dispatch_skinny_norm<NF, MCH, U, WV, XS, false>(a, epi, s);
+  return dispatch_skinny_norm<NF, WV, false, XS>(a, epi, s);
 }
 
-// The skinny variants built for one 16-token chunk, as (rows per workgroup /
-// 16, slabs unrolled per wave, waves per workgroup, staged activations): the
-// ones the selection in gemm() takes.
-#define HS_SKINNY_MCH1(X)                                                                      \
-  X(1, 1, 8, false) X(2, 1, 8, false) X(2, 1, 4, false) X(4, 1, 4, false) X(2, 1, 2, false) \
-  X(4, 1, 2, false) X(8, 1, 2, false) X(1, 1, 16, false) X(3, 1, 16, false) X(1, 1, 16, true)
-
-hipError_t dispatch_skinny1(const GemmArgs& a, int epi, int nf, int u, int wv, bool xs,
-                            hipStream_t s) {
-#define HS_SKINNY_CASE(NF_, U_, WV_, XS_)                  \
-  if (nf == NF_ && u == U_ && wv == WV_ && xs == XS_) \
-    return dispatch_epi_skinny<NF_, 1, U_, WV_, XS_>(a, epi, s);
-  HS_SKINNY_MCH1(HS_SKINNY_CASE)
+hipError_t dispatch_skinny(const GemmArgs& a, int epi, int nf, int wv, bool xs, hipStream_t s) {
+#define HS_SKINNY_CASE(NF_, WV_, XS_) \
+  if (nf == NF_ && wv == WV_ && xs == XS_) return dispatch_epi_skinny<NF_, WV_, XS_>(a, epi, s);
+  HS_SKINNY_BUILDS(HS_SKINNY_CASE)
 #undef HS_SKINNY_CASE
   return hipErrorInvalidValue;
 }
@@ -1120,6 +1093,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
   if (((uintptr_t)a.X | (uintptr_t)a.W | (uintptr_t)a.Y) & 15) return hipErrorInvalidValue;
   if (a.norm_gain && (a.M > 16 || (a.K % 64) || ((uintptr_t)a.norm_gain & 15)))
     return hipErrorInvalidValue;
+  if (!pull_ok(a.pull) || (a.pull.n16 && a.M > 16)) return hipErrorInvalidValue;
   // 32-bit byte offsets in the buffer loads
   if ((uint64_t)a.N * kp * 2 >= (1ull << 31) || (uint64_t)a.M * a.ldx * 2 >= (1ull << 31))
     return hipErrorInvalidValue;
@@ -1135,48 +1109,45 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     // a QKV projection with RoPE runs as a plain (head-order) store followed
     // by the rotation pass
     const int pe = epi == EPI_QKV_ROPE ? EPI_STORE : epi;
-    // Rows per workgroup (16 NF), 64-k slabs per load group (U), waves per
-    // workgroup (WV) and staged activations (XS) for one token chunk, from
-    // sweeps on MI355X over the decode projections of 7B, 8B and 13B models
-    // at 1, 4, 8 and 16 tokens: o and down projections up to one row tile
-    // per CU run sixteen waves of one row tile (7B down at 1 and 8 tokens:
-    // 17.4 -> 16.2 and 18.2 -> 16.9 us against eight waves and two slabs per
-    // group), with the activations staged from 8 tokens on; wider ones eight
-    // waves, two row tiles above 4 tokens. QKV up to 8192 wide takes eight
-    // waves, wide QKV and gate/up four; gate/up takes four row tiles per
-    // workgroup once that still gives 1.5 workgroups per CU (8B, 13B: 38 and
-    // 45 instead of 43 and 52 us); the LM head runs two waves over as many
-    // row tiles as keep about a thousand workgroups (128256 wide: 155 instead
-    // of 162-169 us). WV depends on the shape only, never on M, so that a
-    // token's result (its k order) does not depend on how many tokens share
-    // the call; XS changes only how the same operands reach the MFMAs.
-    // HS_SKINNY_CFG="<NF>,<U>,<WV>[,<XS>]" forces a choice (tuning only; read
-    // on every call so that a sweep can change it between calls).
+    // Rows per workgroup (16 NF), waves per workgroup (WV) and staged
+    // activations (XS), from sweeps on MI355X over the decode projections
+    // of 7B, 8B and 13B models at 1, 4, 8 and 16 tokens (us at 1 token): o and
+    // down projections up to one row tile per CU run sixteen waves of one row
+    // tile (7B down 15.5, eight waves 18.9), wider ones eight waves of two (13B
+    // down 23.8, of one 26.2). QKV up to 8192 wide takes eight waves of two
+    // (8B 11.0, four waves 14.3), wider ones three row tiles when that gives
+    // one workgroup per CU (7B 18.3, two of four waves 18.6), else four waves of
+    // four while that fills three quarters of the CUs (13B 25.4 and, at 16
+    // tokens, 25.1 against 26.4 with two). Gate/up runs two waves of four row
+    // tiles, of two where four leave fewer than 1.5 workgroups per CU (8B 35.7,
+    // four waves 39.1; 7B at 16 tokens 30.2 against 32.7); the LM head two waves
+    // over as many row tiles as keep about a thousand workgroups. Two or
+    // four slabs requested ahead per wave instead of one were 1-10 % slower
+    // nearly everywhere: the waves of a CU keep enough in flight. Activations
+    // are staged from 8 tokens on in the o and down projections, which take no
+    // norm. WV depends on the shape only, never on M, so that a token's result (its k order) does
+    // not depend on how many tokens share the call.
+    // HS_SKINNY_CFG="<NF>,1,<WV>[,<XS>]" forces a choice (tuning only; read on
+    // every call so that a sweep can change it between calls).
     const char* force = getenv("HS_SKINNY_CFG");
     const int cus = device_cus();
-    int nf = 1, u = 1, wv = 4, xs = 0;
+    int nf = 2, wv = 2, xs = 0;
     if (pe == EPI_F32) {
-      nf = 2, wv = 2;
       while (nf < 8 && a.N / (16 * nf) > 1100) nf *= 2;
     } else if (pe == EPI_SWIGLU) {
-      nf = (a.N / 64 >= cus + cus / 2) ? 4 : 2;
+      if (a.N / 64 >= cus + cus / 2) nf = 4;
     } else if (pe == EPI_RESID) {
-      wv = 8;
-      if (a.N / 16 > cus) {
-        nf = a.M > 4 ? 2 : 1;
-      } else {
-        wv = 16;
-        xs = a.M >= 8;
-      }
+      xs = a.M >= 8;
+      if (a.N / 16 > cus) wv = 8;
+      else nf = 1, wv = 16;
     } else if (pe == EPI_STORE) {
-      nf = 2, wv = a.N <= 8192 ? 8 : 4;
-      // three row tiles when that gives one workgroup per CU (7B QKV: 256 x
-      // 48 rows; 21.5 -> 19.5 us)
+      wv = a.N <= 8192 ? 8 : 4;
       if (a.N % 48 == 0 && a.N / 48 <= cus && a.N / 48 > cus * 3 / 4) nf = 3, wv = 16;
+      else if (wv == 4 && a.N / 64 > cus * 3 / 4) nf = 4;
     }
-    if (force && *force) sscanf(force, "%d,%d,%d,%d", &nf, &u, &wv, &xs);
+    if (force && *force) sscanf(force, "%d,%*d,%d,%d", &nf, &wv, &xs);
     if (pe == EPI_SWIGLU && (nf % 2)) nf = 2;
-    e = dispatch_skinny1(a, pe, nf, u, wv, xs != 0, s);
+    e = dispatch_skinny(a, pe, nf, wv, xs != 0, s);
     if (e == hipSuccess && epi == EPI_QKV_ROPE) {
       RopeKvArgs r{static_cast<bf16_t*>(a.Y), a.ldy, a.rope_pos, a.rope_slot, a.rope_cos,
                    a.rope_sin, a.rope_pool, a.M, a.rope_q_cols / a.rope_d,

@@ -8,28 +8,26 @@ namespace hs {
 
 // ------------------------------------------------------------ call metadata
 //
-// A stage call's metadata (positions, slots, tiles, block tables) is written
-// by the host into pinned memory and pulled into device memory by this kernel
-// at the start of the call. A kernel launch follows the previous kernel
-// directly, whereas a copy command waits behind a fence of its own (about
-// 5.5 us of idle GPU on MI355X). The loads are system-coherent (sc0 sc1), so
-// they see what the host wrote before the launch, never a cached copy of an
-// earlier call's values.
+// What the host writes for a call (positions, slots, tiles, block tables; the
+// descriptors of a KV copy) goes into pinned memory and is pulled into device
+// memory by workgroups of a kernel: a copy command would wait behind a fence of
+// its own (about 5.5 us of idle GPU on MI355X). A prefill or decode call's
+// metadata is pulled by extra workgroups of its first kernel (embedding, norm
+// or QKV projection), which does not read it; a launch of its own took 3.9 us
+// of every call. A KV copy's descriptors have this kernel.
 
 // Workgroups [0, b0) copy the first segment, the rest the second.
-__global__ __launch_bounds__(256) void meta_pull_kernel(const int32_t* h0, int32_t* d0,
-                                                        int64_t n0, const int32_t* h1,
-                                                        int32_t* d1, int64_t n1, int b0) {
-  const bool first = (int)blockIdx.x < b0;
-  const int64_t i = (int64_t)(first ? blockIdx.x : blockIdx.x - b0) * 256 + threadIdx.x;
-  const int64_t n16 = first ? n0 : n1;
-  if (i >= n16) return;
-  typedef unsigned u32x4_v __attribute__((ext_vector_type(4)));
-  constexpr int kSystem = 1 | 16;  // sc0 | sc1
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<int32_t*>(first ? h0 : h1), 0, (int)(n16 * 16), 0x00020000);
-  const u32x4_v v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(i * 16), 0, kSystem);
-  *reinterpret_cast<u32x4_v*>((first ? d0 : d1) + i * 4) = v;
+__global__ __launch_bounds__(256) void meta_pull_kernel(const int32_t* h0, int32_t* d0, int n0,
+                                                        const int32_t* h1, int32_t* d1, int n1,
+                                                        int b0) {
+  const int b = blockIdx.x;
+  if (b < b0) pull16(h0, d0, n0, b * 256 + threadIdx.x);
+  else pull16(h1, d1, n1, (b - b0) * 256 + threadIdx.x);
+}
+
+bool pull_ok(const MetaPull& p) {
+  return p.n16 >= 0 && p.n16 < (1 << 27) &&
+         (p.n16 == 0 || (p.host && p.dev && !(((uintptr_t)p.host | (uintptr_t)p.dev) & 15)));
 }
 
 hipError_t meta_pull(const int32_t* host, int32_t* dev, int64_t n, hipStream_t s,
@@ -41,15 +39,17 @@ hipError_t meta_pull(const int32_t* host, int32_t* dev, int64_t n, hipStream_t s
   const int b0 = (int)((n / 4 + 255) / 256), b1 = (int)((n2 / 4 + 255) / 256);
   if (b0 + b1 == 0) return hipSuccess;
   hipLaunchKernelGGL(meta_pull_kernel, dim3((unsigned)(b0 + b1)), dim3(256), 0, s, host, dev,
-                     n / 4, host2, dev2, n2 / 4, b0);
+                     (int)(n / 4), host2, dev2, (int)(n2 / 4), b0);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- embedding
 
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* tok, const bf16_t* E, int vocab,
-                                                    int hidden, bf16_t* out) {
-  const int t = blockIdx.x;
+                                                    int hidden, bf16_t* out, MetaPull pull,
+                                                    int pull_blocks) {
+  const int t = (int)blockIdx.x - pull_blocks;
+  if (t < 0) return pull16(pull.host, pull.dev, pull.n16, blockIdx.x * 256 + threadIdx.x);
   const int id = tok[t];
   const bool ok = id >= 0 && id < vocab;  // out-of-range ids give a zero row
   const int chunks = hidden / 8;
@@ -60,10 +60,12 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* tok, const bf
 }
 
 hipError_t embed(const int32_t* tok, const bf16_t* E, int vocab, int hidden, int n_tok,
-                 bf16_t* out, hipStream_t s, LaunchInfo* info) {
+                 bf16_t* out, hipStream_t s, LaunchInfo* info, const MetaPull& pull) {
   if (n_tok <= 0) return hipSuccess;
-  if (hidden % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_kernel, dim3(n_tok), dim3(256), 0, s, tok, E, vocab, hidden, out);
+  if ((hidden % 8) || !pull_ok(pull)) return hipErrorInvalidValue;
+  const int pb = pull.blocks(256);
+  hipLaunchKernelGGL(embed_kernel, dim3(n_tok + pb), dim3(256), 0, s, tok, E, vocab, hidden, out,
+                     pull, pb);
   if (info) *info = LaunchInfo{"embed", 0, 4.0 * n_tok * (double)hidden};
   return hipGetLastError();
 }
@@ -76,9 +78,11 @@ hipError_t embed(const int32_t* tok, const bf16_t* E, int vocab, int hidden, int
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const bf16_t* x, int64_t ldx,
                                                       const int32_t* rows, int hidden,
                                                       const bf16_t* gain, float eps, bf16_t* out,
-                                                      int64_t ldo) {
+                                                      int64_t ldo, MetaPull pull,
+                                                      int pull_blocks) {
   __shared__ float red[4];
-  const int r = blockIdx.x;
+  const int r = (int)blockIdx.x - pull_blocks;
+  if (r < 0) return pull16(pull.host, pull.dev, pull.n16, blockIdx.x * 256 + threadIdx.x);
   const int src = rows ? rows[r] : r;
   const bf16_t* xr = x + (int64_t)src * ldx;
   const int chunks = hidden / 8;
@@ -125,11 +129,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const bf16_t* x, int64_t l
 
 hipError_t rmsnorm(const bf16_t* x, int64_t ldx, const int32_t* rows, int n_rows, int hidden,
                    const bf16_t* g, float eps, bf16_t* out, int64_t ldo, hipStream_t s,
-                   LaunchInfo* info) {
+                   LaunchInfo* info, const MetaPull& pull) {
   if (n_rows <= 0) return hipSuccess;
-  if ((hidden % 8) || hidden > 8192 || (ldx % 8) || (ldo % 8)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rmsnorm_kernel, dim3(n_rows), dim3(256), 0, s, x, ldx, rows, hidden, g, eps,
-                     out, ldo);
+  if ((hidden % 8) || hidden > 8192 || (ldx % 8) || (ldo % 8) || !pull_ok(pull))
+    return hipErrorInvalidValue;
+  const int pb = pull.blocks(256);
+  hipLaunchKernelGGL(rmsnorm_kernel, dim3(n_rows + pb), dim3(256), 0, s, x, ldx, rows, hidden, g,
+                     eps, out, ldo, pull, pb);
   if (info) *info = LaunchInfo{"rmsnorm", 0, 4.0 * n_rows * (double)hidden};
   return hipGetLastError();
 }
@@ -211,7 +217,10 @@ __device__ __forceinline__ void better(float& v, int& i, float v2, int i2) {
 
 // Two passes: workgroups of the first take 4096-column chunks of a row (four
 // 16-byte loads per thread, all in flight together) and leave the chunk's
-// best (value, index); the second reduces a row's chunks in chunk order.
+// best (value, index); the second reduces a row's chunks in chunk order (a
+// vocabulary of one chunk needs no second). Having the last workgroup of a row
+// to arrive reduce it instead measured 10.6 us against 4.7 + 4.0 (16 rows of
+// 128256, MI355X): every workgroup then waits for its store and its count.
 // Ties go to the lowest index in both, so the result is the row's lowest
 // index of the maximum.
 constexpr int kArgmaxChunk = 4096;
@@ -226,7 +235,8 @@ __device__ __forceinline__ void wave_best(float& bv, int& bi) {
 }
 
 __global__ __launch_bounds__(256) void argmax_chunk_kernel(const float* logits, int n_cols,
-                                                           int n_chunks, int32_t* part) {
+                                                           int n_chunks, int32_t* part,
+                                                           int32_t* out) {
   __shared__ float sv[4];
   __shared__ int si[4];
   const int chunk = blockIdx.x, row = blockIdx.y;
@@ -259,6 +269,10 @@ __global__ __launch_bounds__(256) void argmax_chunk_kernel(const float* logits, 
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) better(bv, bi, sv[w], si[w]);
+    if (n_chunks == 1) {
+      out[row] = bi;
+      return;
+    }
     int32_t* o = part + ((int64_t)row * n_chunks + chunk) * 2;
     o[0] = __float_as_int(bv);
     o[1] = bi;
@@ -286,8 +300,9 @@ hipError_t argmax_rows(const float* logits, int n_rows, int n_cols, int32_t* par
   if (n_cols <= 0 || (n_cols % 4) || !part) return hipErrorInvalidValue;
   const int nc = argmax_chunks(n_cols);
   hipLaunchKernelGGL(argmax_chunk_kernel, dim3(nc, n_rows), dim3(256), 0, s, logits, n_cols, nc,
-                     part);
-  hipLaunchKernelGGL(argmax_final_kernel, dim3(n_rows), dim3(64), 0, s, part, nc, out);
+                     part, out);
+  if (nc > 1)
+    hipLaunchKernelGGL(argmax_final_kernel, dim3(n_rows), dim3(64), 0, s, part, nc, out);
   if (info) *info = LaunchInfo{"argmax", 0, 4.0 * n_rows * (double)n_cols};
   return hipGetLastError();
 }

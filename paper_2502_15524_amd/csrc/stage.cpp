@@ -97,6 +97,7 @@ struct hs_stage {
   hipEvent_t last_done = nullptr;
   bool last_valid = false;
   int cur_meta = -1;      // metadata slot of the call in progress
+  MetaPull pull;          // its metadata, until the call's first kernel takes it
   bool cur_desc = false;  // the call in progress pulled copy descriptors
 
   std::map<uint64_t, Chunk> chunks;
@@ -317,15 +318,23 @@ hs_status meta_acquire(hs_stage* st, Meta* m) {
   return HS_OK;
 }
 
-// Pull the call's metadata into device memory; the slot's event is recorded
-// when the call ends (end_call).
-hs_status meta_upload(hs_stage* st, const Meta& m, hipStream_t s) {
+// Have the call's first kernel pull its metadata into device memory; the
+// slot's event is recorded when the call ends (end_call).
+hs_status meta_arm(hs_stage* st, const Meta& m) {
   if (m.overflow || m.used * 4 > st->meta_bytes) return fail(HS_EINVAL, "internal: metadata overflow");
   st->cur_meta = m.slot;
   st->meta_used[m.slot] = true;
-  const hipError_t e = meta_pull(m.h, m.d, (int64_t)m.used, s);
-  if (e != hipSuccess) return fail(HS_EHIP, hip_msg("metadata pull", e));
+  st->pull.host = m.h;
+  st->pull.dev = m.d;
+  st->pull.n16 = (int)(m.used / 4);
   return HS_OK;
+}
+
+// The pull still to be done by this call (none after its first kernel).
+MetaPull take_pull(hs_stage* st) {
+  const MetaPull p = st->pull;
+  st->pull = MetaPull();
+  return p;
 }
 
 // Is [b, e) covered by submitted chunks? Appends the events still pending.
@@ -454,7 +463,8 @@ hs_status layer_forward_(hs_stage* st, int l, bf16_t* x, const LayerCall& c, hip
   hs_status r;
   if (!fuse_norm) {
     r = run(st, s, "attn_norm", [&](LaunchInfo* i) {
-      return rmsnorm(xr, H, nullptr, c.T, H, W(st, ls.attn_norm), m.rms_eps, st->w_u, H, s, i);
+      return rmsnorm(xr, H, nullptr, c.T, H, W(st, ls.attn_norm), m.rms_eps, st->w_u, H, s, i,
+                     take_pull(st));
     });
     if (r != HS_OK) return r;
   }
@@ -462,7 +472,11 @@ hs_status layer_forward_(hs_stage* st, int l, bf16_t* x, const LayerCall& c, hip
     GemmArgs g = fuse_norm
                      ? gemm_args(st, xr, H, W(st, ls.qkv), st->w_qkv, NQKV, nullptr, 0, c.T, NQKV, H)
                      : gemm_args(st, st->w_u, H, W(st, ls.qkv), st->w_qkv, NQKV, nullptr, 0, c.T, NQKV, H);
-    if (fuse_norm) g.norm_gain = W(st, ls.attn_norm), g.norm_eps = m.rms_eps;
+    if (fuse_norm) {
+      g.norm_gain = W(st, ls.attn_norm);
+      g.norm_eps = m.rms_eps;
+      g.pull = take_pull(st);
+    }
     // the image stores q and k heads with their RoPE halves interleaved
     g.rope_q_cols = QD;
     g.rope_kv_cols = m.n_kv_heads * D;
@@ -527,13 +541,21 @@ hs_status head_forward(hs_stage* st, const bf16_t* x, const int32_t* rows, int n
                        int32_t* out, hipStream_t s) {
   const hs_model_cfg& m = st->cfg;
   const int H = m.hidden;
-  hs_status r = run(st, s, "final_norm", [&](LaunchInfo* i) {
-    return rmsnorm(x, H, rows, n, H, W(st, st->L.final_norm), m.rms_eps, st->w_last, H, s, i);
-  });
-  if (r != HS_OK) return r;
+  // a decode batch of up to 16 rows: the head applies the norm, as the layers'
+  // projections do
+  const bool fuse_norm = !rows && n <= 16;
+  hs_status r = HS_OK;
+  if (!fuse_norm) {
+    r = run(st, s, "final_norm", [&](LaunchInfo* i) {
+      return rmsnorm(x, H, rows, n, H, W(st, st->L.final_norm), m.rms_eps, st->w_last, H, s, i);
+    });
+    if (r != HS_OK) return r;
+  }
   float* lg = logits ? logits : st->w_logits;
   r = run(st, s, "lm_head", [&](LaunchInfo* i) {
-    GemmArgs g = gemm_args(st, st->w_last, H, W(st, st->L.lm_head), lg, m.vocab, nullptr, 0, n, m.vocab, H);
+    GemmArgs g = gemm_args(st, fuse_norm ? x : st->w_last, H, W(st, st->L.lm_head), lg, m.vocab,
+                           nullptr, 0, n, m.vocab, H);
+    if (fuse_norm) g.norm_gain = W(st, st->L.final_norm), g.norm_eps = m.rms_eps;
     return gemm(g, EPI_F32, s, i);
   });
   if (r != HS_OK) return r;
@@ -1117,7 +1139,7 @@ extern "C" hs_status hs_stage_prefill(hs_stage* st, int32_t n, const int64_t* id
   r = begin_call(st, s);
   if (r != HS_OK) return r;
   CallEnd ce{st, s};
-  r = meta_upload(st, mt, s);
+  r = meta_arm(st, mt);
   if (r != HS_OK) return r;
 
   const int H = st->cfg.hidden;
@@ -1127,7 +1149,7 @@ extern "C" hs_status hs_stage_prefill(hs_stage* st, int32_t n, const int64_t* id
     if (r != HS_OK) return r;
     r = run(st, s, "embed", [&](LaunchInfo* i) {
       return embed(static_cast<const int32_t*>(in), W(st, st->L.embed), st->cfg.vocab, H, (int)T,
-                   x, s, i);
+                   x, s, i, take_pull(st));
     });
     if (r != HS_OK) return r;
   }
@@ -1223,7 +1245,7 @@ extern "C" hs_status hs_stage_decode(hs_stage* st, int32_t n, const int64_t* ids
   r = begin_call(st, s);
   if (r != HS_OK) return r;
   CallEnd ce{st, s};
-  r = meta_upload(st, mt, s);
+  r = meta_arm(st, mt);
   if (r != HS_OK) return r;
 
   const int H = st->cfg.hidden;
@@ -1232,7 +1254,8 @@ extern "C" hs_status hs_stage_decode(hs_stage* st, int32_t n, const int64_t* ids
     r = wait_need(s, ne[0]);
     if (r != HS_OK) return r;
     r = run(st, s, "embed", [&](LaunchInfo* i) {
-      return embed(static_cast<const int32_t*>(in), W(st, st->L.embed), st->cfg.vocab, H, n, x, s, i);
+      return embed(static_cast<const int32_t*>(in), W(st, st->L.embed), st->cfg.vocab, H, n, x, s, i,
+                   take_pull(st));
     });
     if (r != HS_OK) return r;
   }
