@@ -667,7 +667,8 @@ __global__ __launch_bounds__(256) void attn_decode_split_kernel(AttnDecodeArgs a
   __shared__ float s_ml[4][G][2];
   __shared__ float s_acc[4][G][D];
 
-  const int split = blockIdx.x, kh = blockIdx.y, b = blockIdx.z;
+  const int split = blockIdx.x / a.n_kv_heads, kh = blockIdx.x - split * a.n_kv_heads;
+  const int b = blockIdx.y;
   // the split's block-table entries are loaded together with the context
   // length: one round trip before the key/value loads instead of two
   const int32_t* bt = a.block_table + (int64_t)b * a.max_blocks;
@@ -914,7 +915,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void a
   static_assert(G * D * 4 <= 32 * LV * 2, "a wave's partial fits its value buffer");
   const auto s_acc = [&](int w) { return reinterpret_cast<float*>(sV[w]); };
 
-  const int split = blockIdx.x, kh = blockIdx.y, b = blockIdx.z;
+  const int split = blockIdx.x / a.n_kv_heads, kh = blockIdx.x - split * a.n_kv_heads;
+  const int b = blockIdx.y;
   const int32_t* bt = a.block_table + (int64_t)b * a.max_blocks;
   int phys[BPS];
 #pragma unroll
@@ -1135,7 +1137,15 @@ __global__ __launch_bounds__(D) void attn_decode_combine_kernel(AttnDecodeArgs a
 namespace {
 template <int D, int G>
 void launch_split(const AttnDecodeArgs& a, float sl, hipStream_t s) {
-  dim3 grid(a.call_splits, a.n_kv_heads, a.B);
+  // kv heads fastest, so that the eight XCDs (workgroup i runs on XCD i mod 8)
+  // share every split of every sequence. With the splits fastest and a multiple
+  // of eight of them, an XCD had the same splits of all sequences, and those
+  // with the late splits, which only long sequences have, stood idle. Split
+  // kernel, MI355X, splits -> kv heads fastest: 8B heads, 32 sequences of 256 to
+  // 4096 71.0 -> 54.3 us (5.4 TB/s), 16 of 128 to 2048 20.8 -> 17.5; 13B, 40 of 64
+  // to 1024 99.2 -> 74.5 (6.2 TB/s), 16 of 200 to 3000 104 -> 99; 7B, 8 of about
+  // 1100 24.9 -> 25.8.
+  dim3 grid(a.n_kv_heads * a.call_splits, a.B);
   static const char* force = getenv("HS_DECODE_ATTN");  // "valu" (tuning only)
   if constexpr (D == 128 && G >= 2) {
     if (!(force && strcmp(force, "valu") == 0)) {
@@ -1167,6 +1177,7 @@ hipError_t attn_decode(const AttnDecodeArgs& a, hipStream_t s, LaunchInfo* info)
   if (a.B <= 0) return hipSuccess;
   if ((a.D != 64 && a.D != 128) || a.n_kv_heads <= 0 || a.n_heads % a.n_kv_heads) return hipErrorInvalidValue;
   if (a.call_splits <= 0 || a.call_splits > a.max_splits || (a.ldq % 8)) return hipErrorInvalidValue;
+  if ((int64_t)a.call_splits * a.n_kv_heads >= (1ll << 31)) return hipErrorInvalidValue;
   if (a.pool_w && (!a.cos_t || !a.sin_t || a.max_pos <= 0 || a.pool_w != a.pool))
     return hipErrorInvalidValue;
   // byte offsets of one (query head, sequence)'s partials fit 32 bits
