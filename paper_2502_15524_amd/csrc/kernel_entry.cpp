@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -95,6 +96,72 @@ extern "C" hs_status hs_k_gemm_rmsnorm(const void* X, int64_t ldx, const void* g
   }
 }
 
+namespace {
+// Sequence offsets and tiles of hs_k_attn_prefill: pinned memory the host
+// writes and its device copy, pulled by a kernel. A call takes a pair for its
+// duration (it waits for its work before it gives the pair back); up to four
+// idle pairs per device, of at most 256 KiB each, are kept for later calls, in
+// place of an allocation, two copies and a free in every call.
+struct MetaBuf {
+  int32_t *h = nullptr, *d = nullptr;
+  size_t cap = 0;
+  int dev = -1;
+};
+constexpr size_t kMetaMin = 1 << 12, kMetaKeep = 1 << 16, kMetaIdle = 4;
+std::mutex g_meta_mu;
+std::vector<MetaBuf> g_meta_idle[64];
+
+void meta_free(const MetaBuf& m) {
+  if (m.h) (void)hipHostFree(m.h);
+  if (m.d) (void)hipFree(m.d);
+}
+
+bool meta_take(size_t n, MetaBuf* out) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  {
+    std::lock_guard<std::mutex> lock(g_meta_mu);
+    auto& idle = g_meta_idle[dev];
+    for (size_t i = 0; i < idle.size(); ++i)
+      if (idle[i].cap >= n) {
+        *out = idle[i];
+        idle.erase(idle.begin() + i);
+        return true;
+      }
+  }
+  MetaBuf m;
+  m.cap = std::max(n, kMetaMin);
+  m.dev = dev;
+  if (hipHostMalloc(reinterpret_cast<void**>(&m.h), m.cap * 4, hipHostMallocCoherent) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&m.d), m.cap * 4) != hipSuccess) {
+    meta_free(m);
+    return false;
+  }
+  *out = m;
+  return true;
+}
+
+void meta_give(const MetaBuf& m) {
+  if (m.cap <= kMetaKeep) {
+    std::lock_guard<std::mutex> lock(g_meta_mu);
+    auto& idle = g_meta_idle[m.dev];
+    if (idle.size() == kMetaIdle)  // a smaller one makes room
+      for (auto& o : idle)
+        if (o.cap < m.cap) {
+          const MetaBuf small = o;
+          o = m;
+          meta_free(small);
+          return;
+        }
+    if (idle.size() < kMetaIdle) {
+      idle.push_back(m);
+      return;
+    }
+  }
+  meta_free(m);
+}
+}  // namespace
+
 extern "C" hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t* cu, int32_t n,
                                        int32_t n_heads, int32_t n_kv_heads, int32_t head_dim,
                                        void* stream) {
@@ -120,19 +187,20 @@ extern "C" hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t
       tiles.push_back(-t.first);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t* d = nullptr;
-    const size_t nb = (size_t)(n + 1 + tiles.size()) * 4;
-    if (hipMalloc(reinterpret_cast<void**>(&d), nb) != hipSuccess)
-      return fail(HS_ENOMEM, "device allocation failed");
-    hipError_t e = hipMemcpy(d, cu, (n + 1) * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(d + n + 1, tiles.data(), tiles.size() * 4, hipMemcpyHostToDevice);
+    const size_t cu_n = ((size_t)n + 1 + 3) / 4 * 4, need = (cu_n + tiles.size() + 3) / 4 * 4;
+    MetaBuf m;
+    if (!meta_take(need, &m)) return fail(HS_ENOMEM, "metadata allocation failed");
+    std::copy(cu, cu + n + 1, m.h);
+    std::copy(tiles.begin(), tiles.end(), m.h + cu_n);
     const int ld = (n_heads + 2 * n_kv_heads) * head_dim;
     AttnPrefillArgs a{static_cast<const bf16_t*>(qkv), ld, static_cast<bf16_t*>(out),
-                      n_heads * head_dim, d, d + n + 1, (int)(tiles.size() / 2), n_heads,
+                      n_heads * head_dim, m.d, m.d + cu_n, (int)(tiles.size() / 2), n_heads,
                       n_kv_heads, head_dim, waves, 16 * waves, 0.0};
+    hipError_t e = meta_pull(m.h, m.d, (int64_t)need, s);
     if (e == hipSuccess) e = attn_prefill(a, s, nullptr);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(d);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    meta_give(m);
     return launched(e, "attn_prefill");
   } catch (...) {
     return fail(HS_EINVAL, "unexpected internal error");
