@@ -255,7 +255,7 @@ def gemm_shapes(reps=20, copies=4):
     a stage; beside them torch.matmul (hipBLASLt) of the same operands, which
     writes the plain product (no residual read, no SwiGLU halving). Random
     bf16 operands (timing only). QKV runs with the plain-store epilogue here;
-    in a stage, prompts of more than 64 tokens rotate and append in the QKV
+    in a stage, prompts of more than 16 tokens rotate and append in the QKV
     epilogue and decode batches fold the RMSNorm into QKV and gate/up."""
     import torch
     from paper_2502_15524_amd import hs
@@ -1042,11 +1042,11 @@ def bench_kernel_name(rocprof_name):
     if m:
         sk = "sk" if m.group(3) == "true" else ""
         return f"gemm_r{m.group(1)}x{m.group(2)}{sk}_{_EPI_NAMES[int(m.group(4))]}", "k_gemm"
-    m = re.search(r"gemm_skinny<\d+, \d+, \d+, (\d+), (true|false), \d+[,>]", rocprof_name)
+    m = re.search(r"gemm_skinny<\d+, (\d+), (true|false), \d+[,>]", rocprof_name)
     if m:
         norm = "norm_" if m.group(2) == "true" else ""
         return f"gemm_skinny_{norm}{_EPI_NAMES[int(m.group(1))]}", "k_gemm"
-    m = re.search(r"attn_prefill_kernel<(\d+),", rocprof_name)
+    m = re.search(r"attn_prefill(?:_wide)?_kernel<(\d+)[,>]", rocprof_name)
     if m:
         return f"attn_prefill_d{m.group(1)}", "k_attn"
     if "attn_decode" in rocprof_name:
