@@ -70,6 +70,33 @@ __device__ __forceinline__ float silu_f(float g) {
   return g / (1.0f + fast_exp2(-g * 1.4426950408889634f));
 }
 
+// Copies from global memory straight into LDS. The instruction takes its LDS
+// address from M0; a scalar write of M0 needs one wait state before a load that
+// reads it, and the assembler adds none inside inline assembly: hence the s_nop
+// (one issue slot per 1 KiB).
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+
+constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data format
+
+__device__ __forceinline__ v4i_t buf_rsrc(const void* p, uint64_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint32_t n = bytes >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes;
+  return v4i_t{(int)(uint32_t)a, (int)(uint32_t)((a >> 32) & 0xFFFFu), (int)n, kRsrcWord3};
+}
+
+// 64 lanes x 16 bytes from rsrc + voff + soff into LDS bytes [lds, lds + 1024)
+__device__ __forceinline__ void dma16(v4i_t rsrc, int voff, int soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)),
+                  "s"(__builtin_amdgcn_readfirstlane(lds))
+               : "memory", "m0");
+}
+__device__ __forceinline__ void dma16(v4i_t rsrc, int voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               :: "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(lds))
+               : "memory", "m0");
+}
+
 // One thread's 16 bytes of a pull from pinned host memory (units i of n16): the
 // loads are system-coherent (sc0 sc1), so they see what the host wrote before
 // the launch, never a cached copy of an earlier call's values.

@@ -31,19 +31,6 @@ namespace hs {
 // fragment, whose row addresses follow the same key permutation.
 
 typedef short s16x4_v __attribute__((ext_vector_type(4)));
-typedef int v4i_at __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4i_at attn_rsrc(const void* p, uint32_t bytes) {
-  const uint64_t u = reinterpret_cast<uint64_t>(p);
-  return v4i_at{(int)(uint32_t)u, (int)(uint32_t)((u >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
-
-// 64 lanes x 16 bytes from rsrc + voff into LDS bytes [lds, lds + 1024)
-__device__ __forceinline__ void attn_dma16(v4i_at rsrc, int voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               :: "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(lds))
-               : "memory");
-}
 
 // chunk swizzles of the wide form's key and value rows
 template <int D>
@@ -327,12 +314,12 @@ void attn_prefill_wide_kernel(AttnPrefillArgs a, float scale_log2) {
   auto request = [&](int kb) {
     const char* kp = kbase + (int64_t)kb * KB * row_bytes;
     const uint32_t bytes = (uint32_t)(min(len - kb * KB, KB) - 1) * row_bytes + ROW;
-    const v4i_at rk = attn_rsrc(kp, bytes), rv = attn_rsrc(kp + v_off, bytes);
+    const v4i_t rk = buf_rsrc(kp, bytes), rv = buf_rsrc(kp + v_off, bytes);
     const uint32_t to = lds0 + (kb & 1) * 2 * BLK + wave * PER * 1024;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) attn_dma16(rk, ko[i], to + i * 1024);
+    for (int i = 0; i < PER; ++i) dma16(rk, ko[i], to + i * 1024);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) attn_dma16(rv, vo[i], to + BLK + i * 1024);
+    for (int i = 0; i < PER; ++i) dma16(rv, vo[i], to + BLK + i * 1024);
   };
   request(0);
 

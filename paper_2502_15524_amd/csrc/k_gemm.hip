@@ -152,24 +152,6 @@ __device__ __forceinline__ void store_qkv_rope(const GemmArgs& a, int m, int slo
 // barrier. K is processed in 64-column slabs; when K % 64 != 0 the activation
 // columns up to the next multiple of 64 must be zero (the weights are).
 
-typedef int v4i_t __attribute__((ext_vector_type(4)));
-
-constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data format
-
-__device__ __forceinline__ v4i_t buf_rsrc(const void* p, uint64_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  const uint32_t n = bytes >= 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)bytes;
-  return v4i_t{(int)(uint32_t)a, (int)(uint32_t)((a >> 32) & 0xFFFFu), (int)n, kRsrcWord3};
-}
-
-// 64 lanes x 16 bytes from rsrc + voff + soff into LDS bytes [lds, lds + 1024)
-__device__ __forceinline__ void dma16(v4i_t rsrc, int voff, int soff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :: "v"(voff), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane(soff)),
-                  "s"(__builtin_amdgcn_readfirstlane(lds))
-               : "memory");
-}
-
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
