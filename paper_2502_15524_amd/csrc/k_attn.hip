@@ -358,8 +358,9 @@ void attn_prefill_wide_kernel(AttnPrefillArgs a, float scale_log2) {
 
   auto open_block = [&](int kb) {
     // this wave's copies of the block have landed; with everybody's at the
-    // barrier, where also every wave is done with the other stage
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // barrier, where also every wave is done with the other stage (its last
+    // reads complete, not merely issued)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
     if (kb + 1 < n_kb) request(kb + 1);
   };

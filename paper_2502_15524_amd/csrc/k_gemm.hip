@@ -158,6 +158,13 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
+// the same, and every LDS read of this wave is complete
+template <int N>
+__device__ __forceinline__ void wait_vm_lds() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory");
+}
+
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // Eight waves per workgroup, two per SIMD, as 2 x 4: two wave columns over the
@@ -189,7 +196,9 @@ __device__ __forceinline__ int chunk_pos(int r, int c) {
 // row tile i run, and the B fragments of the next 32-k step are read with the
 // first A fragment that needs them. The last row tile of a stage is deferred
 // past the workgroup barrier: it runs while the next stage's first fragments
-// come from LDS (its operands are already in registers).
+// come from LDS. Its operands have to be in registers by that barrier, after
+// which any wave may refill the stage: the wave waits for its reads (lgkmcnt)
+// together with its copies.
 template <int CPR>
 __device__ __forceinline__ bf16x8_v lds_frag(const bf16_t* s, int r, int c) {
   return as_bf16x8(ld16(s + (r * CPR + chunk_pos<CPR>(r, c)) * 8));
@@ -581,8 +590,10 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
           for (int q = step * LPS / USE; q < (step + 1) * LPS / USE; ++q) issue(j + AHEAD, q);
         }
       });
-      if (more) wait_vm<(NS - 2) * LPS>();
-      else wait_vm<0>();
+      // slab j's stage is refilled, by any wave, right after the barrier: the
+      // deferred row tile's operands have to be in registers by then
+      if (more) wait_vm_lds<(NS - 2) * LPS>();
+      else wait_vm_lds<0>();
       wg_barrier();
     }
     // the last stage's deferred row tile

@@ -68,3 +68,34 @@ def test_m0_is_written_a_wait_state_before_a_load_into_lds(kernels):
                     bad.append(name)
     assert loads > 100
     assert not bad, {n: bad.count(n) for n in sorted(set(bad))}
+
+
+def test_no_lds_read_is_outstanding_when_its_stage_is_given_up(kernels):
+    """The pipelined kernels refill a stage of LDS from any wave right after the
+    barrier that ends its use, so each wave's reads of it have to be complete at
+    that barrier (lgkmcnt 0 after the last read), not merely issued. The
+    ping-pong loop (last template argument true) refills two barriers after a
+    read: its reads may pass one."""
+    seen = 0
+    for name, ins in kernels.items():
+        if "gemm_ring<" in name:
+            passes = 1 if re.search(r"true>\(", name) else 0
+        elif "attn_prefill_wide_kernel" in name:
+            passes = 0
+        else:
+            continue
+        seen += 1
+        out = None  # barriers passed since the oldest read that may be outstanding
+        barriers = 0
+        for x in ins:
+            if x.startswith("ds_read"):
+                out = 0 if out is None else out
+            elif x.startswith("s_waitcnt") and "lgkmcnt(0)" in x:
+                out = None
+            elif x.startswith("s_barrier"):
+                barriers += 1
+                if out is not None:
+                    out += 1
+                    assert out <= passes, (name, barriers)
+        assert barriers, name
+    assert seen > 50
