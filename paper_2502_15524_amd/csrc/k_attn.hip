@@ -263,8 +263,8 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnPrefillArgs a, fl
 //
 // Keeping a query's running max while a block's is at most 8 above it (log2)
 // saves most rescaling and 3-5 % of the time, but the largest weight is then
-// rounded too: error against 64 bits 0.00206 of the norm instead of 0.00191
-// (0.00192 for the narrow form), so the max is exact.
+// rounded too: error against 64 bits 0.00206 of the norm instead of 0.00191, so
+// the max is exact.
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_prefill_wide_kernel(AttnPrefillArgs a, float scale_log2) {
@@ -425,24 +425,23 @@ void attn_prefill_wide_kernel(AttnPrefillArgs a, float scale_log2) {
 #pragma unroll
       for (int i = 0; i < D / 32; ++i) o[i] *= corr;
     }
-    // The sum is of the rounded probabilities the product uses (float32, two
-    // at a time by v_dot2), so that the weights of a row add up to one: their
-    // rounding errors cancel where one key dominates.
-    float psum[2] = {0.f, 0.f};
+    // the sum is of the float32 probabilities, as in the narrow form (of the
+    // rounded ones, which the product uses, it would err with their rounding
+    // where many keys of small weight hold values near zero)
+    float psum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[t][e] = fast_exp2(__builtin_fmaf(s[t][e], scale_log2, -m_run));
+      for (int e = 0; e < 16; ++e) {
+        s[t][e] = fast_exp2(__builtin_fmaf(s[t][e], scale_log2, -m_run));
+        psum[e & 3] += s[t][e];
+      }
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
       pack8 pb;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < 4; ++w)
         pb.w[w] = pack2bf(s[st >> 1][8 * (st & 1) + 2 * w], s[st >> 1][8 * (st & 1) + 2 * w + 1]);
-        psum[w & 1] = __builtin_amdgcn_fdot2_f32_bf16(
-            __builtin_bit_cast(bf16x2_v, pb.w[w]), __builtin_bit_cast(bf16x2_v, 0x3F803F80u),
-            psum[w & 1], false);
-      }
       const bf16x8_v pf = as_bf16x8(pb);
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt) {
@@ -452,7 +451,7 @@ void attn_prefill_wide_kernel(AttnPrefillArgs a, float scale_log2) {
       }
       if (st + 2 < 4) read_v(st + 2);
     }
-    l_run += psum[0] + psum[1];
+    l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
   };
   // the wave's queries lie in one 64-key block, its diagonal one: the blocks
   // before it need no mask, those after it only their barrier (so do all

@@ -271,6 +271,52 @@ def test_attn_prefill_value_ones_gives_ones():
     assert np.max(np.abs(got - 1.0)) <= 2 ** -7
 
 
+@pytest.mark.parametrize("lens,nh,nkv,d", [([64, 63], 4, 2, 128), ([1024], 32, 8, 128), ([1000, 700], 16, 4, 64)])
+def test_attn_prefill_row_sums_are_not_rounded(lens, nh, nkv, d):
+    """Rows of one dominant key with values and many keys of equal small weight
+    with none: the output is v0 / (1 + n p), so an error of the row sum shows
+    in every column alike. p = 2^-k 1.0036 rounds to 2^-k in bf16 (0.36 % off, half
+    a unit in its last place); summed like that, a row with n p = 1 is 0.18 %
+    off. The output's own rounding (up to 2^-8 = 0.4 %) averages out over columns
+    and rows."""
+    torch = G.torch()
+    hs = _hs()
+    T = sum(lens)
+    rng = np.random.default_rng(T + d)
+    scale_log2 = np.log2(np.e) / np.sqrt(d)
+    logn = int(np.log2(max(lens)))
+    delta = (-logn + np.log2(1.0036)) / scale_log2      # score of a small key; the dominant one's is 0
+    q = np.zeros((T, nh, d), np.float32)
+    k = np.zeros((T, nkv, d), np.float32)
+    v = np.zeros((T, nkv, d), np.float32)
+    q[:, :, :3] = 1.0
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    parts = []
+    for _ in range(3):                                  # delta as a sum of three bf16 values
+        parts.append(float(gen.round_to_bf16(np.float32([delta - sum(parts)]))[0]))
+    k[:, :, :3] = parts
+    for i in range(len(lens)):
+        k[cu[i], :, :3] = 0.0
+        v[cu[i]] = gen.round_to_bf16(rng.standard_normal((nkv, d)).astype(np.float32))
+    qkv = np.concatenate([x.reshape(T, -1) for x in (q, k, v)], axis=1)
+    out = torch.zeros((T, nh * d), dtype=torch.bfloat16, device="cuda")
+    hs.hs_k_attn_prefill(G.to_dev_bf16(qkv).data_ptr(), out.data_ptr(), list(cu), nh, nkv, d, G.stream_ptr())
+    torch.cuda.synchronize()
+    got = G.from_dev_bf16(out).reshape(T, nh, d)
+    p = 2.0 ** (sum(parts) * scale_log2)
+    assert abs(p * 2.0 ** logn - 1.0036) < 1e-4
+    for i, n in enumerate(lens):
+        rows = np.arange(n // 2, n)                     # n p of 0.25 and more
+        v0 = np.repeat(v[cu[i]], nh // nkv, axis=0).astype(np.float64)
+        ref = v0[None] / (1.0 + rows * p)[:, None, None]
+        err = (got[cu[i] + rows] / ref - 1.0)
+        assert np.abs(err).max() <= 1.01 * 2.0 ** -8
+        # roundings of up to +-2^-8 (standard deviation 2.3e-3 or less) over the
+        # columns and kv heads of 32 rows or more: 3e-5 or less; a rounded sum is
+        # off by 0.36 % n p / (1 + n p), 7e-4 or more
+        assert abs(err.mean()) <= 2.5e-4, (i, err.mean())
+
+
 def _paged_case(lens, nh, nkv, d, seed):
     """Random post-RoPE keys/values of ragged sequences scattered over a KV
     pool [blocks][K|V][nkv][16][d] in a shuffled block order."""
