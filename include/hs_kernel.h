@@ -27,12 +27,15 @@ extern "C" {
  * K % 8 == 0, N % 16 == 0 (N % 32 for SwiGLU), 16-byte aligned X, W, Y; if
  * K % 64 != 0, ldx must be at least K rounded up to 64 and the extra columns
  * of X zero. This is the projection arithmetic of every decoder layer (QKV,
- * O, gate/up, down) and of the LM head. Shapes with few output tiles split
- * their k range over workgroups; the partial sums go through a workspace
- * that the library allocates once per device (32 MiB + 1 KiB, on the
- * first call) and keeps until the process ends, so calls on one device must not
- * run concurrently. Results are deterministic: the same inputs give the same
- * bits on every call. */
+ * O, gate/up, down) and of the LM head. From 17 rows on, shapes with few
+ * output tiles split their k range over workgroups; the partial sums go through
+ * workspaces that the library allocates once per device (on the first call of
+ * their size) and keeps until the process ends. Calls of up to 16 rows use none;
+ * those of 17 to 64 rows share one of 8 MiB + 1 KiB and may come from any stream
+ * or thread (the library orders the launches that split; a captured launch is
+ * ordered by the caller); calls of more than 64 rows share one of 32 MiB +
+ * 1 KiB and must not run concurrently on one device. Results are
+ * deterministic: the same inputs give the same bits on every call. */
 hs_status hs_k_gemm(const void* X, int64_t ldx, const void* W, void* Y, int64_t ldy,
                     const void* R, int64_t ldr, int32_t M, int32_t N, int32_t K, int32_t epi,
                     void* stream);
@@ -44,7 +47,7 @@ hs_status hs_k_gemm(const void* X, int64_t ldx, const void* W, void* Y, int64_t 
  * by the gain and rounded to bf16 on the way into the product, and each
  * output row is scaled by its 1 / RMS in float32 afterwards. For decode
  * batches: requires 1 <= M <= 16 and K % 64 == 0 (HS_EINVAL otherwise);
- * other arguments, epilogues and the workspace as hs_k_gemm. */
+ * other arguments and epilogues as hs_k_gemm. */
 hs_status hs_k_gemm_rmsnorm(const void* X, int64_t ldx, const void* g, float eps, const void* W,
                             void* Y, int64_t ldy, const void* R, int64_t ldr, int32_t M,
                             int32_t N, int32_t K, int32_t epi, void* stream);

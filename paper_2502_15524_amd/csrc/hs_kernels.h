@@ -70,6 +70,7 @@ struct LaunchInfo {
   const char* name;
   double flops;
   double bytes;
+  bool split = false;  // a GEMM that used the workspace of split tiles
 };
 
 hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info);

@@ -1098,6 +1098,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
                            (epi == EPI_RESID ? 2 : 1);
   const double bytes = 2.0 * ((double)a.M * a.K + (double)a.N * a.K) + out_bytes;
   hipError_t e;
+  bool split = false;
   if (a.M <= 16) {
     // a QKV projection with RoPE runs as a plain (head-order) store followed
     // by the rotation pass
@@ -1209,12 +1210,14 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     const long grid = tiles * sc.split;
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     e = launch_ring(*cfg, a, epi, sc, (int)grid, s);
+    split = sc.split > 1;
     snprintf(name, sizeof name, "gemm_r%s%s_%s", cfg->name, sc.split > 1 ? "sk" : "", kEpiName[epi]);
   }
   if (info) {
     info->name = name;
     info->flops = flops;
     info->bytes = bytes;
+    info->split = split;
   }
   return e;
 }

@@ -15,34 +15,46 @@
 using namespace hs;
 
 namespace {
-// Split-k workspace of hs_k_gemm, one per device, allocated on first use and
-// kept until the process ends (calls on one device must not overlap).
+// Workspaces of hs_k_gemm's split tiles, allocated per device on first use and
+// kept until the process ends. Calls of more than 64 rows on one device must not
+// overlap. Calls of 17 to 64 rows have a workspace of their own (an 128 x 64
+// partial tile per workgroup), whose launches are put one after the other by an
+// event: calls of that size may come from several streams and threads.
 struct GemmWs {
   float* part = nullptr;
   uint32_t* flags = nullptr;
+  hipEvent_t done = nullptr;  // small: after the last launch that used it
+  bool used = false;
 };
 constexpr int64_t kWsPartFloats = 256ll * 256 * 128;  // a 256 x 128 partial tile per workgroup
+constexpr int64_t kWsSmallFloats = 256ll * 128 * 64;
 constexpr int64_t kWsFlags = 256;
+std::mutex g_gemm_mu;  // both workspaces, and a small call's wait, launch and record
 
-hs_status gemm_ws(GemmWs** out) {
-  static GemmWs ws[64];
+// (with g_gemm_mu held)
+hs_status gemm_ws(bool small, GemmWs** out) {
+  static GemmWs ws[2][64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
     return fail(HS_EHIP, "hipGetDevice failed");
-  GemmWs& w = ws[dev];
+  GemmWs& w = ws[small][dev];
   if (!w.part) {
     float* p = nullptr;
     uint32_t* f = nullptr;
-    if (hipMalloc(&p, kWsPartFloats * sizeof(float)) != hipSuccess) return fail(HS_ENOMEM, "gemm workspace");
+    hipEvent_t ev = nullptr;
+    const int64_t floats = small ? kWsSmallFloats : kWsPartFloats;
+    if (hipMalloc(&p, floats * sizeof(float)) != hipSuccess) return fail(HS_ENOMEM, "gemm workspace");
     if (hipMalloc(&f, kWsFlags * sizeof(uint32_t)) != hipSuccess ||
         hipMemset(f, 0, kWsFlags * sizeof(uint32_t)) != hipSuccess ||
-        hipDeviceSynchronize() != hipSuccess) {
+        hipDeviceSynchronize() != hipSuccess ||
+        (small && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess)) {
       (void)hipFree(p);
       if (f) (void)hipFree(f);
       return fail(HS_ENOMEM, "gemm workspace");
     }
     w.part = p;
     w.flags = f;
+    w.done = ev;
   }
   *out = &w;
   return HS_OK;
@@ -56,14 +68,34 @@ hs_status launched(hipError_t e, const char* what) {
 }  // namespace
 
 hs_status gemm_call(GemmArgs a, int32_t epi, void* stream) {
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (a.M <= 16) return launched(gemm(a, epi, s, nullptr), "gemm");  // no workspace
+  const bool small = a.M <= 64;
+  std::unique_lock<std::mutex> lock(g_gemm_mu);
   GemmWs* ws = nullptr;
-  const hs_status r = gemm_ws(&ws);
+  const hs_status r = gemm_ws(small, &ws);
   if (r != HS_OK) return r;
   a.part = ws->part;
-  a.part_floats = kWsPartFloats;
+  a.part_floats = small ? kWsSmallFloats : kWsPartFloats;
   a.flags = ws->flags;
   a.flags_n = kWsFlags;
-  return launched(gemm(a, epi, static_cast<hipStream_t>(stream), nullptr), "gemm");
+  if (!small) {
+    lock.unlock();
+    return launched(gemm(a, epi, s, nullptr), "gemm");
+  }
+  // (a captured launch cannot wait for work outside its graph: the caller
+  // orders the graph's replays)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(s, &cap);
+  const bool ordered = cap == hipStreamCaptureStatusNone;
+  if (e == hipSuccess && ordered && ws->used) e = hipStreamWaitEvent(s, ws->done, 0);
+  LaunchInfo info{"", 0, 0};
+  if (e == hipSuccess) e = gemm(a, epi, s, &info);
+  if (e == hipSuccess && ordered && info.split) {
+    ws->used = true;
+    e = hipEventRecord(ws->done, s);
+  }
+  return launched(e, "gemm");
 }
 
 extern "C" hs_status hs_k_gemm(const void* X, int64_t ldx, const void* Wt, void* Y, int64_t ldy,

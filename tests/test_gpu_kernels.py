@@ -180,6 +180,61 @@ def test_gemm_tile_configurations(cfg, M, N, K, epi, monkeypatch):
     assert np.abs(outs[0] - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
 
 
+def test_gemm_small_batches_from_two_streams(monkeypatch):
+    """17 to 64 rows, split over workgroups, from two threads with a stream each:
+    every result has the bits of the same call made alone."""
+    monkeypatch.setenv("HS_GEMM_CFG", "64x64,sk")
+    import threading
+    torch = G.torch()
+    hs = _hs()
+    rng = np.random.default_rng(5)
+    cases = []
+    for M, N, K in ((40, 512, 4096), (64, 256, 8192), (17, 1024, 2048), (33, 512, 4096)):
+        X = rng.standard_normal((M, K)).astype(np.float32)
+        Wt = (rng.standard_normal((N, K)) * 0.05).astype(np.float32)
+        dX = G.to_dev_bf16(X)
+        dW = torch.from_numpy(G.tile_bits(gen.to_bf16_bits(gen.round_to_bf16(Wt))).view(np.int16)).cuda()
+        cases.append((M, N, K, dX, dW))
+
+    def call(c, Y, sp):
+        M, N, K, dX, dW = c
+        hs.hs_k_gemm(dX.data_ptr(), K, dW.data_ptr(), Y.data_ptr(), N, 0, N, M, N, K, "f32", sp)
+
+    alone = []
+    for c in cases:
+        Y = torch.zeros((c[0], c[1]), dtype=torch.float32, device="cuda")
+        call(c, Y, G.stream_ptr())
+        torch.cuda.synchronize()
+        ref = G.from_dev_bf16(c[3]).astype(np.float64) @ G.untile_bits(
+            gen.bf16_bits_to_f32(c[4].cpu().numpy().view(np.uint16)), c[1], c[2]).astype(np.float64).T
+        assert np.abs(Y.cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max()
+        alone.append(Y.cpu().numpy())
+    reps, errors = 20, []
+    orders = [list(range(len(cases))), list(range(len(cases)))[::-1]]
+    outs = [[torch.zeros(alone[i].shape, dtype=torch.float32, device="cuda") for _ in range(reps) for i in order]
+            for order in orders]
+    torch.cuda.synchronize()
+
+    def work(t):
+        try:
+            s = torch.cuda.Stream()
+            for n, i in enumerate(orders[t] * reps):
+                call(cases[i], outs[t][n], s.cuda_stream)
+            s.synchronize()
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for t in range(2):
+        for n, i in enumerate(orders[t] * reps):
+            assert np.array_equal(outs[t][n].cpu().numpy(), alone[i]), (t, n, i)
+
+
 # 7B-shape projections at a 512-token prompt: few output tiles, so their k
 # ranges are split across workgroups (stream-K). Rows are sampled for the
 # float64 reference; two calls must agree bitwise.
