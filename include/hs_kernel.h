@@ -5,7 +5,8 @@
  * exactly as the stage forward pass launches it. They exist so that each
  * kernel can be checked against a reference and timed on its own; serving
  * goes through hs.h. All pointers are device pointers owned by the caller;
- * `stream` is a hipStream_t (NULL = the null stream). Work is asynchronous.
+ * `stream` is a hipStream_t (NULL = the null stream). Work is asynchronous,
+ * except where an entry says that it waits.
  * Shapes the kernel does not support return HS_EINVAL before any launch.
  */
 #ifndef HS_KERNEL_H
@@ -55,7 +56,11 @@ hs_status hs_k_gemm_rmsnorm(const void* X, int64_t ldx, const void* g, float eps
 /* Causal grouped-query attention over packed sequences (the attention of the
  * prefill pass). qkv: bf16 [T][(n_heads + 2 n_kv_heads) head_dim] holding
  * post-RoPE q, k, v per token; out: bf16 [T][n_heads head_dim]; cu_seqlens:
- * HOST int32 [n_seqs + 1] token offsets (cu[0] = 0, cu[n] = T). */
+ * HOST int32 [n_seqs + 1] token offsets (cu[0] = 0, cu[n] = T). The offsets
+ * reach the GPU through a pinned buffer and its device copy that the call has to
+ * itself: it waits for its work on `stream`, so it cannot be captured, and may
+ * come from any stream or thread. Up to four such pairs of at most 256 KiB
+ * each are kept per device until the process ends. */
 hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t* cu_seqlens,
                             int32_t n_seqs, int32_t n_heads, int32_t n_kv_heads,
                             int32_t head_dim, void* stream);

@@ -131,9 +131,9 @@ extern "C" hs_status hs_k_gemm_rmsnorm(const void* X, int64_t ldx, const void* g
 namespace {
 // Sequence offsets and tiles of hs_k_attn_prefill: pinned memory the host
 // writes and its device copy, pulled by a kernel. A call takes a pair for its
-// duration (it waits for its work before it gives the pair back); up to four
-// idle pairs per device, of at most 256 KiB each, are kept for later calls, in
-// place of an allocation, two copies and a free in every call.
+// duration: it gives the pair back only after a successful wait for its work.
+// Up to four idle pairs per device, of at most 256 KiB each, are kept for later
+// calls, in place of an allocation, two copies and a free in every call.
 struct MetaBuf {
   int32_t *h = nullptr, *d = nullptr;
   size_t cap = 0;
@@ -173,24 +173,21 @@ bool meta_take(size_t n, MetaBuf* out) {
   return true;
 }
 
-void meta_give(const MetaBuf& m) {
+void meta_give(MetaBuf m) {
   if (m.cap <= kMetaKeep) {
     std::lock_guard<std::mutex> lock(g_meta_mu);
     auto& idle = g_meta_idle[m.dev];
-    if (idle.size() == kMetaIdle)  // a smaller one makes room
-      for (auto& o : idle)
-        if (o.cap < m.cap) {
-          const MetaBuf small = o;
-          o = m;
-          meta_free(small);
-          return;
-        }
     if (idle.size() < kMetaIdle) {
       idle.push_back(m);
       return;
     }
+    for (auto& o : idle)
+      if (o.cap < m.cap) {  // a smaller one makes room
+        std::swap(o, m);
+        break;
+      }
   }
-  meta_free(m);
+  meta_free(m);  // waits for the device: not with the mutex held
 }
 }  // namespace
 
@@ -232,7 +229,9 @@ extern "C" hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t
     if (e == hipSuccess) e = attn_prefill(a, s, nullptr);
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess) e = es;
-    meta_give(m);
+    // after a failed wait the queued work may still read the pair: it is left
+    // allocated, to no other call
+    if (es == hipSuccess) meta_give(m);
     return launched(e, "attn_prefill");
   } catch (...) {
     return fail(HS_EINVAL, "unexpected internal error");

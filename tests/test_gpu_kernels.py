@@ -372,6 +372,48 @@ def test_attn_prefill_row_sums_are_not_rounded(lens, nh, nkv, d):
         assert abs(err.mean()) <= 2.5e-4, (i, err.mean())
 
 
+def test_attn_prefill_from_three_threads():
+    """Calls of different lengths (and metadata sizes) from three threads, each
+    with a stream of its own: the bits of the same call made alone."""
+    import threading
+    torch = G.torch()
+    hs = _hs()
+    nh, nkv, d = 4, 2, 64
+    rng = np.random.default_rng(9)
+    cases = []
+    for lens in ([5, 70], [300], [1] * 1500, [130, 257, 64]):
+        cu = [0] + [int(x) for x in np.cumsum(lens)]
+        qkv = G.to_dev_bf16(rng.standard_normal((cu[-1], (nh + 2 * nkv) * d)).astype(np.float32))
+        cases.append((cu, qkv))
+
+    def call(i, sp):
+        cu, qkv = cases[i]
+        out = torch.zeros((cu[-1], nh * d), dtype=torch.bfloat16, device="cuda")
+        torch.cuda.synchronize()
+        hs.hs_k_attn_prefill(qkv.data_ptr(), out.data_ptr(), cu, nh, nkv, d, sp)
+        return out
+
+    alone = [G.from_dev_bf16(call(i, G.stream_ptr())) for i in range(len(cases))]
+    errors = []
+
+    def work(t):
+        try:
+            s = torch.cuda.Stream()
+            for r in range(6):
+                i = (r + t) % len(cases)
+                if not np.array_equal(G.from_dev_bf16(call(i, s.cuda_stream)), alone[i]):
+                    errors.append((t, r, i))
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+
+
 def _paged_case(lens, nh, nkv, d, seed):
     """Random post-RoPE keys/values of ragged sequences scattered over a KV
     pool [blocks][K|V][nkv][16][d] in a shuffled block order."""
