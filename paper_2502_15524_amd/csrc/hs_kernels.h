@@ -62,7 +62,7 @@ struct GemmArgs {
   const float* rope_cos = nullptr; const float* rope_sin = nullptr;
   int rope_max_pos = 0;
   bf16_t* rope_pool = nullptr;
-  MetaPull pull;  // M <= 16 only
+  MetaPull pull;  // M <= 16 with norm_gain only
 };
 
 // Describes what was launched (for timing).

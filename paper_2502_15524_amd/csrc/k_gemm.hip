@@ -740,7 +740,10 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 // an image laid out and read like a weight tile's. The MFMA operands are the
 // same; whole rows pay off from 8 tokens on, where the activations the previous
 // kernel wrote come from beyond the XCD's L2 (8B layer at 16 tokens, in the
-// decode step: o and down 36.6 -> 31.6 us together).
+// decode step: o and down 36.6 -> 31.6 us together). XS = 1 requests them one slab
+// ahead, as below; XS = 2 after the next slab's weights: from 13 tokens on the
+// one-row-tile form is faster so (16 tokens x 4096 x 11008 17.87 -> 17.61 us, x
+// 14336 22.44 -> 22.05; 8 tokens 15.50 against 15.89 and 19.24 against 19.57).
 //
 // A slab's loads are issued as its registers come free, weights before
 // activations, so no wait for one slab covers a later one's loads. (Loads
@@ -756,17 +759,21 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 // of the raw values are summed along the way, and the epilogue scales each
 // token's outputs by 1 / sqrt(mean square + eps). Used for decode, where the
 // separate norm kernel would cost a launch per projection.
-template <int NF, int EPI, bool NORM, int WV, bool XS>
+template <int NF, int EPI, bool NORM, int WV, int XS>
 __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
   static_assert(EPI != EPI_SWIGLU || (NF % 2) == 0, "SwiGLU needs gate/up tile pairs");
   // the norm's sums of squares follow the fragment-order loads; keeping one
   // order for every batch size keeps a token's result independent of M
   static_assert(!(NORM && XS), "staged activations are built without the fused norm");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // a call's first kernel also pulls its metadata, in its first workgroups
-  const int pb = a.pull.blocks(64 * WV);
-  if ((int)blockIdx.x < pb)
-    return pull16(a.pull.host, a.pull.dev, a.pull.n16, blockIdx.x * 64 * WV + threadIdx.x);
+  // a call's first kernel also pulls its metadata, in its first workgroups (it
+  // applies a norm: gemm() refuses a pull without one)
+  int pb = 0;
+  if constexpr (NORM) {
+    pb = a.pull.blocks(64 * WV);
+    if ((int)blockIdx.x < pb)
+      return pull16(a.pull.host, a.pull.dev, a.pull.n16, blockIdx.x * 64 * WV + threadIdx.x);
+  }
   const int n0 = ((int)blockIdx.x - pb) * 16 * NF;
   const int kp = (a.K + 63) & ~63;
   const int nslab = kp / 64;
@@ -776,7 +783,13 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
   const int slab_bytes = (a.N / 8) * 1024;
   // Loads past a wave's last slab, of row tiles past N and of tokens past M
   // get an offset past the end of their buffer: they read zeros and touch no
-  // memory, and no load is behind a branch (the waits stay exact).
+  // memory, and no load is behind a branch (the waits stay exact). With one row
+  // tile a workgroup there is little to wait for in order, and the loads past
+  // the last slab cost more than a uniform branch around them (4096 rows of
+  // weights, MI355X, past -> branch: K = 4096 7.66 -> 7.30 us at 1 token and 8.20 ->
+  // 7.70 at 8, K = 14336 18.73 -> 18.42 and, at 16, 22.66 -> 22.31; with two row
+  // tiles, 5120 x 13824, 23.5 -> 23.9).
+  constexpr bool kBranch = NF == 1;
   constexpr int kPast = (int)0x80000000u;
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(a.W), 0, (int)((int64_t)a.N * kp * 2), kRsrcWord3);
@@ -835,7 +848,7 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
             rw, ((wbase + sl * slab_bytes) | past | wpast[f]) + (2 * f + h) * 1024, 0, kNt);
   };
   load_w(sb);
-  load_x(sb);
+  if constexpr (XS != 2) load_x(sb);
   for (int sl = sb; sl < se; ++sl) {
     // this wave's buffer: the previous slab's fragment reads were issued
     // before these stores, and one wave's LDS operations run in order
@@ -844,7 +857,8 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
         wlds[wave][(2 * f + h) * 64 + lane] = __builtin_bit_cast(pack8, wv[f][h]);
-    load_w(sl + 1);
+    if (!kBranch || sl + 1 < se) load_w(sl + 1);
+    if constexpr (XS == 2) load_x(sl);
     pack8 xc[2], gc[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
@@ -852,7 +866,9 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
       if constexpr (XS) wlds[wave][NF * 128 + ks * 64 + lane] = xc[ks];
       if constexpr (NORM) gc[ks] = __builtin_bit_cast(pack8, gv[ks]);
     }
-    load_x(sl + 1);
+    if constexpr (XS != 2) {
+      if (!kBranch || sl + 1 < se) load_x(sl + 1);
+    }
     if constexpr (NORM) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
@@ -922,7 +938,7 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
 
 namespace {
 
-template <int NF, int WV, bool NORM, bool XS>
+template <int NF, int WV, bool NORM, int XS>
 hipError_t dispatch_skinny_norm(const GemmArgs& a, int epi, hipStream_t s) {
   const int grid = (a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV);
   const dim3 blk(64 * WV);
@@ -950,20 +966,20 @@ hipError_t dispatch_skinny_norm(const GemmArgs& a, int epi, hipStream_t s) {
 
 // The skinny variants, as (rows per workgroup / 16, waves per workgroup,
 // staged activations): the ones the selection in gemm() takes.
-#define HS_SKINNY_BUILDS(X)                                                    \
-  X(2, 8, false) X(2, 4, false) X(4, 4, false) X(2, 2, false) X(4, 2, false) \
-  X(8, 2, false) X(1, 16, false) X(3, 16, false) X(1, 16, true) X(2, 8, true)
+#define HS_SKINNY_BUILDS(X)                                        \
+  X(2, 8, 0) X(2, 4, 0) X(4, 4, 0) X(2, 2, 0) X(4, 2, 0) X(8, 2, 0) \
+  X(1, 16, 0) X(3, 16, 0) X(1, 16, 1) X(1, 16, 2) X(2, 8, 1)
 
-template <int NF, int WV, bool XS>
+template <int NF, int WV, int XS>
 hipError_t dispatch_epi_skinny(const GemmArgs& a, int epi, hipStream_t s) {
   if (a.norm_gain) {
-    if constexpr (!XS) return dispatch_skinny_norm<NF, WV, true, false>(a, epi, s);
+    if constexpr (!XS) return dispatch_skinny_norm<NF, WV, true, 0>(a, epi, s);
     else return hipErrorInvalidValue;
   }
   return dispatch_skinny_norm<NF, WV, false, XS>(a, epi, s);
 }
 
-hipError_t dispatch_skinny(const GemmArgs& a, int epi, int nf, int wv, bool xs, hipStream_t s) {
+hipError_t dispatch_skinny(const GemmArgs& a, int epi, int nf, int wv, int xs, hipStream_t s) {
 #define HS_SKINNY_CASE(NF_, WV_, XS_) \
   if (nf == NF_ && wv == WV_ && xs == XS_) return dispatch_epi_skinny<NF_, WV_, XS_>(a, epi, s);
   HS_SKINNY_BUILDS(HS_SKINNY_CASE)
@@ -1086,7 +1102,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
   if (((uintptr_t)a.X | (uintptr_t)a.W | (uintptr_t)a.Y) & 15) return hipErrorInvalidValue;
   if (a.norm_gain && (a.M > 16 || (a.K % 64) || ((uintptr_t)a.norm_gain & 15)))
     return hipErrorInvalidValue;
-  if (!pull_ok(a.pull) || (a.pull.n16 && a.M > 16)) return hipErrorInvalidValue;
+  if (!pull_ok(a.pull) || (a.pull.n16 && (a.M > 16 || !a.norm_gain))) return hipErrorInvalidValue;
   // 32-bit byte offsets in the buffer loads
   if ((uint64_t)a.N * kp * 2 >= (1ull << 31) || (uint64_t)a.M * a.ldx * 2 >= (1ull << 31))
     return hipErrorInvalidValue;
@@ -1133,7 +1149,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     } else if (pe == EPI_RESID) {
       xs = a.M >= 8;
       if (a.N / 16 > cus) wv = 8;
-      else nf = 1, wv = 16;
+      else nf = 1, wv = 16, xs += a.M > 12;
     } else if (pe == EPI_STORE) {
       wv = a.N <= 8192 ? 8 : 4;
       if (a.N % 48 == 0 && a.N / 48 <= cus && a.N / 48 > cus * 3 / 4) nf = 3, wv = 16;
@@ -1141,7 +1157,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     }
     if (force && *force) sscanf(force, "%d,%*d,%d,%d", &nf, &wv, &xs);
     if (pe == EPI_SWIGLU && (nf % 2)) nf = 2;
-    e = dispatch_skinny(a, pe, nf, wv, xs != 0, s);
+    e = dispatch_skinny(a, pe, nf, wv, xs, s);
     if (e == hipSuccess && epi == EPI_QKV_ROPE) {
       RopeKvArgs r{static_cast<bf16_t*>(a.Y), a.ldy, a.rope_pos, a.rope_slot, a.rope_cos,
                    a.rope_sin, a.rope_pool, a.M, a.rope_q_cols / a.rope_d,

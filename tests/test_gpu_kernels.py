@@ -87,7 +87,7 @@ def test_gemm_staged_activations_bitwise(M, N, K):
     outs = []
     old = os.environ.get("HS_SKINNY_CFG")
     try:
-        for xs in (0, 1):
+        for xs in (0, 1, 2):
             os.environ["HS_SKINNY_CFG"] = f"1,1,16,{xs}"
             Y = G.to_dev_bf16(R)
             hs.hs_k_gemm(dX.data_ptr(), K, dW.data_ptr(), Y.data_ptr(), N, Y.data_ptr(), N,
@@ -99,7 +99,7 @@ def test_gemm_staged_activations_bitwise(M, N, K):
             os.environ.pop("HS_SKINNY_CFG", None)
         else:
             os.environ["HS_SKINNY_CFG"] = old
-    assert np.array_equal(outs[0], outs[1])
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
     ref = R + X.astype(np.float64) @ Wt.astype(np.float64).T
     assert np.abs(outs[1] - ref).max() <= 8e-3 * np.abs(ref).max()
 
