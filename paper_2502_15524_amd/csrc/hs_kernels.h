@@ -23,6 +23,8 @@ struct MetaPull {
 
 bool pull_ok(const MetaPull& p);  // alignment and size
 
+int device_cus();  // compute units of the current device
+
 // Epilogues of Y[m][n] = sum_k X[m][k] * W[n][k] (fp32 accumulation).
 enum Epi : int {
   EPI_STORE = 0,   // Y = bf16(acc)
@@ -99,14 +101,13 @@ struct AttnPrefillArgs {
   const int32_t* cu;              // [n_seqs + 1] token offsets
   const int32_t* tiles;           // [n_tiles][2] (sequence, first query row, multiple of q_tile)
   int n_tiles, n_heads, n_kv_heads, D;
-  int waves, q_tile;              // 4 (narrow) or 8 (wide); q_tile = 16 * waves queries per workgroup
+  int q_tile;                     // queries per workgroup: 64 (narrow form) or 128 (wide)
   double flops;                   // unmasked-pair flops, for reporting
 };
 hipError_t attn_prefill(const AttnPrefillArgs& a, hipStream_t s, LaunchInfo* info);
-// Form of the prefill attention for a problem with `tiles_of_128` 128-query
-// tiles (summed over sequences) and n_heads heads: 4 = 64-query tiles, 8 =
-// 128-query tiles.
-int attn_prefill_waves(int64_t tiles_of_128, int n_heads);
+// The queries per workgroup to run a problem with: tiles_of_64 64-query tiles
+// (summed over sequences), the longest sequence and n_heads heads.
+int attn_prefill_q_tile(int64_t tiles_of_64, int longest, int n_heads);
 
 constexpr int kDecodeSplit = 128;  // tokens per split of the decode attention
 

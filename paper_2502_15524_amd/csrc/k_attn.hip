@@ -488,13 +488,13 @@ void attn_prefill_wide_kernel(AttnPrefillArgs a, float scale_log2) {
 hipError_t attn_prefill(const AttnPrefillArgs& a, hipStream_t s, LaunchInfo* info) {
   if (a.n_tiles <= 0) return hipSuccess;
   if ((a.D != 64 && a.D != 128) || a.n_kv_heads <= 0 || a.n_heads % a.n_kv_heads) return hipErrorInvalidValue;
-  if ((a.ld % 8) || (a.ldo % 4) || a.q_tile != 16 * a.waves || (a.waves != 4 && a.waves != 8))
+  if ((a.ld % 8) || (a.ldo % 4) || (a.q_tile != 64 && a.q_tile != 128))
     return hipErrorInvalidValue;
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)a.D));
   dim3 grid(a.n_tiles, a.n_heads);
-  if (a.waves == 8 && a.D == 128)
+  if (a.q_tile == 128 && a.D == 128)
     hipLaunchKernelGGL(attn_prefill_wide_kernel<128>, grid, dim3(256), 0, s, a, scale_log2);
-  else if (a.waves == 8)
+  else if (a.q_tile == 128)
     hipLaunchKernelGGL(attn_prefill_wide_kernel<64>, grid, dim3(256), 0, s, a, scale_log2);
   else if (a.D == 128)
     hipLaunchKernelGGL(attn_prefill_kernel<128>, grid, dim3(512), 0, s, a, scale_log2);
@@ -508,12 +508,18 @@ hipError_t attn_prefill(const AttnPrefillArgs& a, hipStream_t s, LaunchInfo* inf
   return hipGetLastError();
 }
 
-// The narrow form (64-query tiles) while its tiles fit one workgroup per CU,
-// the wide one (128-query tiles) above: MI355X, d = 128, narrow / wide: 512
-// tokens of 32 heads 14.0 / 14.9 us, of 40 heads 21.5 / 15.2, 4 x 300 of 32
-// heads 17.4 / 13.4, 16 x 64 8.6 / 9.2, 1024 37.8 / 25.0, 2048 100 / 53.
-int attn_prefill_waves(int64_t tiles_of_128, int n_heads) {
-  return tiles_of_128 * n_heads > 128 ? 8 : 4;
+// The narrow form (64-query tiles) while its tiles fit one workgroup per CU and
+// a sequence is longer than one of them; the wide one (128-query tiles) above
+// that, and where no sequence has more than 64 tokens: there its two busy waves
+// have half the LDS reads and no merge of two key parts. MI355X, kernel trace,
+// narrow / wide in us, d = 128: 512 tokens of 32 heads 13.8 / 15.6 (256 tiles of
+// 64), of 40 heads 21.3 / 16.5 (320); 4 x 128 of 32 heads 7.8 / 8.1 (256), 2 of
+// 200 to 300 12.4 / 10.6 (288); 1024 of 32 heads 36.5 / 26.4; 64 tokens 6.6 /
+// 5.6, 16 x 64 11.9 / 9.0, 4 x 64 of 4 heads 6.4 / 5.5. Over 135 shapes of 4 to
+// 40 heads and 32 to 2553 tokens the choice is 5 % behind the better form at
+// worst (16 of 100 to 200 tokens of 4 heads).
+int attn_prefill_q_tile(int64_t tiles_of_64, int longest, int n_heads) {
+  return longest <= 64 || tiles_of_64 * n_heads > device_cus() ? 128 : 64;
 }
 
 // ------------------------------------------------------------------- decode

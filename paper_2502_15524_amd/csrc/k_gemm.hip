@@ -1060,6 +1060,10 @@ hipError_t launch_ring(const RingCfg& c, const GemmArgs& a, int epi, const GemmS
   }
 }
 
+const char* kEpiName[5] = {"store", "resid", "swiglu", "f32", "qkv_rope"};
+
+}  // namespace
+
 int device_cus() {
   static int cus[64] = {};
   int dev = 0;
@@ -1073,10 +1077,6 @@ int device_cus() {
   }
   return cus[dev];
 }
-
-const char* kEpiName[5] = {"store", "resid", "swiglu", "f32", "qkv_rope"};
-
-}  // namespace
 
 hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipErrorInvalidValue;

@@ -199,17 +199,19 @@ extern "C" hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t
     if (n_kv_heads < 1 || n_heads % n_kv_heads) return fail(HS_EINVAL, "bad head counts");
     if (cu[0] != 0) return fail(HS_EINVAL, "cu_seqlens[0] must be 0");
     std::vector<int32_t> tiles;
-    int64_t tiles128 = 0;
+    int64_t tiles64 = 0;
+    int longest = 0;
     for (int i = 0; i < n; ++i) {
       const int len = cu[i + 1] - cu[i];
       if (len < 1) return fail(HS_EINVAL, "sequence lengths must be >= 1");
-      tiles128 += (len + 127) / 128;
+      tiles64 += (len + 63) / 64;
+      longest = std::max(longest, len);
     }
-    const int waves = attn_prefill_waves(tiles128, n_heads);
+    const int q_tile = attn_prefill_q_tile(tiles64, longest, n_heads);
     // longest rows first, as the stage orders them
     std::vector<std::pair<int32_t, int32_t>> order;
     for (int i = 0; i < n; ++i)
-      for (int q = 0; q < cu[i + 1] - cu[i]; q += 16 * waves) order.emplace_back(-q, i);
+      for (int q = 0; q < cu[i + 1] - cu[i]; q += q_tile) order.emplace_back(-q, i);
     std::sort(order.begin(), order.end());
     for (const auto& t : order) {
       tiles.push_back(t.second);
@@ -224,7 +226,7 @@ extern "C" hs_status hs_k_attn_prefill(const void* qkv, void* out, const int32_t
     const int ld = (n_heads + 2 * n_kv_heads) * head_dim;
     AttnPrefillArgs a{static_cast<const bf16_t*>(qkv), ld, static_cast<bf16_t*>(out),
                       n_heads * head_dim, m.d, m.d + cu_n, (int)(tiles.size() / 2), n_heads,
-                      n_kv_heads, head_dim, waves, 16 * waves, 0.0};
+                      n_kv_heads, head_dim, q_tile, 0.0};
     hipError_t e = meta_pull(m.h, m.d, (int64_t)need, s);
     if (e == hipSuccess) e = attn_prefill(a, s, nullptr);
     const hipError_t es = hipStreamSynchronize(s);

@@ -433,7 +433,7 @@ struct LayerCall {
   const bf16_t* xin;
   const int32_t *pos, *slot;             // device
   const int32_t *cu, *tiles;             // prefill
-  int n_tiles, attn_waves;
+  int n_tiles, attn_q_tile;
   double attn_flops;
   const int32_t *bt, *ctx;               // decode
   int call_splits;
@@ -494,8 +494,7 @@ hs_status layer_forward_(hs_stage* st, int l, bf16_t* x, const LayerCall& c, hip
   if (!c.decode) {
     r = run(st, s, "attn", [&](LaunchInfo* i) {
       AttnPrefillArgs a{st->w_qkv, NQKV, st->w_attn, QD, c.cu, c.tiles, c.n_tiles,
-                        m.n_heads, m.n_kv_heads, D, c.attn_waves, 16 * c.attn_waves,
-                        c.attn_flops};
+                        m.n_heads, m.n_kv_heads, D, c.attn_q_tile, c.attn_flops};
       return attn_prefill(a, s, i);
     });
   } else {
@@ -1118,10 +1117,13 @@ extern "C" hs_status hs_stage_prefill(hs_stage* st, int32_t n, const int64_t* id
     attn_flops += 4.0 * st->cfg.n_heads * st->cfg.head_dim * 0.5 * (double)lens[i] * (lens[i] + 1);
   }
   // attention work tiles: q_tile queries of one sequence, longest rows first
-  int64_t tiles128 = 0;
-  for (int i = 0; i < n; ++i) tiles128 += (lens[i] + 127) / 128;
-  const int attn_waves = attn_prefill_waves(tiles128, st->cfg.n_heads);
-  const int q_tile = 16 * attn_waves;
+  int64_t tiles64 = 0;
+  int longest = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles64 += (lens[i] + 63) / 64;
+    longest = std::max(longest, (int)lens[i]);
+  }
+  const int q_tile = attn_prefill_q_tile(tiles64, longest, st->cfg.n_heads);
   for (int i = 0; i < n; ++i)
     for (int q = 0; q < lens[i]; q += q_tile) tiles.emplace_back(i, q);
   std::stable_sort(tiles.begin(), tiles.end(),
@@ -1162,7 +1164,7 @@ extern "C" hs_status hs_stage_prefill(hs_stage* st, int32_t n, const int64_t* id
   c.cu = d_cu;
   c.tiles = d_tiles;
   c.n_tiles = (int)tiles.size();
-  c.attn_waves = attn_waves;
+  c.attn_q_tile = q_tile;
   c.attn_flops = attn_flops;
   for (int l = st->begin; l < st->end; ++l) {
     r = wait_need(s, nl[l - st->begin]);

@@ -275,12 +275,15 @@ def test_gemm_split_k_shapes(N, K, epi):
 @pytest.mark.parametrize("lens,nh,nkv,d", [
     ([1], 4, 4, 64), ([5, 64, 65], 4, 2, 64), ([130, 7, 300], 4, 4, 128),
     ([257], 8, 2, 128), ([64, 128, 1, 33], 2, 1, 128),
-    ([1024, 1024], 32, 8, 128),      # enough 128-query tiles for the 8-wave variant
-    # 4-wave tiles that do not fit one workgroup per CU (no key split):
-    # workgroup counts 512 and 380 (D = 128), 320 and 276 (D = 64), so both
-    # multiples of 8 and others
+    ([1024, 1024], 32, 8, 128),
+    # 128-query tiles (their 64-query ones exceed the CUs): workgroup counts 256
+    # and 200 (D = 128), 176 and 144 (D = 64), multiples of 8
     ([1024], 32, 8, 128), ([1000, 150], 20, 5, 128), ([900, 300], 16, 4, 64),
     ([1000, 400], 12, 6, 64),
+    # around the choice of the tile: no sequence above 64 tokens and one of 65;
+    # 256 tiles of 64 queries (one per CU) and 272
+    ([64, 17, 1, 63], 4, 2, 128), ([64, 17, 1, 65], 4, 2, 128), ([33] * 9, 8, 8, 64),
+    ([1024], 16, 4, 64), ([512, 512, 1], 16, 4, 128),
     # 128-query tiles at their edges: sequence ends around 32-query waves,
     # 64-key blocks and tiles; heads in eighths (1, 3, 4 an XCD) and not
     ([1, 31, 33, 63, 64, 65, 127, 128, 129, 191, 257], 32, 8, 128),
