@@ -940,24 +940,24 @@ namespace {
 
 template <int NF, int WV, bool NORM, int XS>
 hipError_t dispatch_skinny_norm(const GemmArgs& a, int epi, hipStream_t s) {
-  const int grid = (a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV);
+  const dim3 grid((a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV));
   const dim3 blk(64 * WV);
   switch (epi) {
     case EPI_STORE:
-      hipLaunchKernelGGL((gemm_skinny<NF, EPI_STORE, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+      hipLaunchKernelGGL((gemm_skinny<NF, EPI_STORE, NORM, WV, XS>), grid, blk, 0, s, a);
       break;
     case EPI_RESID:
-      hipLaunchKernelGGL((gemm_skinny<NF, EPI_RESID, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+      hipLaunchKernelGGL((gemm_skinny<NF, EPI_RESID, NORM, WV, XS>), grid, blk, 0, s, a);
       break;
     case EPI_SWIGLU:
       if constexpr (NF % 2 == 0) {
-        hipLaunchKernelGGL((gemm_skinny<NF, EPI_SWIGLU, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+        hipLaunchKernelGGL((gemm_skinny<NF, EPI_SWIGLU, NORM, WV, XS>), grid, blk, 0, s, a);
         break;
       } else {
         return hipErrorInvalidValue;
       }
     case EPI_F32:
-      hipLaunchKernelGGL((gemm_skinny<NF, EPI_F32, NORM, WV, XS>), dim3(grid), blk, 0, s, a);
+      hipLaunchKernelGGL((gemm_skinny<NF, EPI_F32, NORM, WV, XS>), grid, blk, 0, s, a);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -1115,6 +1115,11 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
   const double bytes = 2.0 * ((double)a.M * a.K + (double)a.N * a.K) + out_bytes;
   hipError_t e;
   bool split = false;
+  // HS_GEMM_CFG="<tile>[,dp|,sk[<ways>]][,g<n>]" forces a choice of
+  // kernel above 16 rows: tile, whole or split tiles, tile group (tuning only;
+  // read on every call so that a sweep can change it between calls).
+  const char* force_cfg = getenv("HS_GEMM_CFG");
+  const bool forced = force_cfg && *force_cfg;
   if (a.M <= 16) {
     // a QKV projection with RoPE runs as a plain (head-order) store followed
     // by the rotation pass
@@ -1167,15 +1172,12 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     snprintf(name, sizeof name, "gemm_skinny_%s%s", a.norm_gain ? "norm_" : "", kEpiName[epi]);
   } else {
     // Configuration by the time model of kRing.
-    // HS_GEMM_CFG="<tile>[,dp|,sk][,g<n>]" forces a choice of tile, whole or
-    // split tiles, and tile group (tuning only; read on every call so that a
-    // sweep can change it between calls).
     const int cus = device_cus();
     const int nk = (int)(kp / 64);
     auto tiles_of = [&](const RingCfg& c) {
       return (long)((a.N + c.bn - 1) / c.bn) * ((a.M + c.bm - 1) / c.bm);
     };
-    // workgroups per tile of a split launch: as many as the chip holds, at
+    // most workgroups per tile of a split launch: as many as the chip holds, at
     // least four slabs each; 1 where a split launch is not possible
     auto split_of = [&](const RingCfg& c, long tiles) -> long {
       const long sp = std::min<long>(cus / tiles, nk / 4);
@@ -1203,16 +1205,37 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
         sk = split < whole;
       }
     }
+    long ways = sk ? split_of(*cfg, tiles_of(*cfg)) : 1;
+    if (a.M <= 64 && cfg->bn == 64) {
+      // How many ways to split a 64 x 64 tile, by times measured up to 64 rows: the
+      // model above was fitted at 80 and more, where a way costs 2.5 us, here 0.6.
+      // Beyond six the merge costs more than the shorter share saves. Whole ->
+      // split, 17 rows: 1024 x 4096 17.4 -> 8.5 us, 2048 x 5632 23.7 -> 10.7, 3072 x
+      // 3072 14.7 -> 9.4; eight ways -> six: 2048 x 8192 13.6 -> 12.6; but a K of 1024
+      // stays whole (5504 x 1024 6.7, two ways 7.7).
+      const long most = std::min<long>(6, split_of(*cfg, tiles_of(*cfg)));
+      double t = 0.9 * (2.8 + 0.235 * nk);
+      ways = 1;
+      for (long w = 2; w <= most; ++w) {
+        const double tw = 3.3 + 0.26 * nk / w + 0.58 * w;
+        if (tw < t) t = tw, ways = w;
+      }
+    }
     int group = 8;
-    const char* force = getenv("HS_GEMM_CFG");  // read per call (tuning sweeps)
-    if (force && *force) {
-      std::string f(force);
+    if (forced) {
+      std::string f(force_cfg);
       for (const RingCfg& c : kRing)  // longest matching name wins
         if (f.compare(0, strlen(c.name), c.name) == 0 &&
             (f.size() == strlen(c.name) || f[strlen(c.name)] == ','))
           cfg = &c;
-      if (f.find(",dp") != std::string::npos) sk = false;
-      if (f.find(",sk") != std::string::npos) sk = true;
+      ways = sk ? split_of(*cfg, tiles_of(*cfg)) : 1;
+      if (f.find(",dp") != std::string::npos) ways = 1;
+      const size_t sp = f.find(",sk");
+      if (sp != std::string::npos) {
+        ways = split_of(*cfg, tiles_of(*cfg));
+        const long n = atoi(f.c_str() + sp + 3);
+        if (n > 0) ways = std::min(ways, n);
+      }
       const size_t gp = f.find(",g");
       if (gp != std::string::npos) group = std::max(1, atoi(f.c_str() + gp + 2));
     }
@@ -1222,7 +1245,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     sc.nk = nk;
     sc.group_n = group;
     const long tiles = (long)sc.tiles_n * sc.tiles_m;
-    sc.split = sk ? (int)split_of(*cfg, tiles) : 1;
+    sc.split = (int)ways;
     const long grid = tiles * sc.split;
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     e = launch_ring(*cfg, a, epi, sc, (int)grid, s);

@@ -180,6 +180,48 @@ def test_gemm_tile_configurations(cfg, M, N, K, epi, monkeypatch):
     assert np.abs(outs[0] - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
 
 
+# 17 to 64 rows of matrices whose tiles stay whole or are split two to six ways.
+@pytest.mark.parametrize("M,N,K,epi", [
+    (17, 256, 688, "resid"), (33, 272, 256, "store"), (64, 400, 712, "f32"),
+    (48, 4112, 320, "resid"),
+    (64, 2048, 2048, "resid"), (64, 2064, 2048, "resid"),
+    (17, 1376, 256, "swiglu"), (33, 2048, 5632, "resid"), (64, 1024, 4096, "swiglu")])
+def test_gemm_17_to_64_rows(M, N, K, epi):
+    torch = G.torch()
+    hs = _hs()
+    rng = np.random.default_rng(M + N + K)
+    X = gen.round_to_bf16(rng.standard_normal((M, K)).astype(np.float32))
+    Wt = gen.round_to_bf16((rng.standard_normal((N, K)) * 0.05).astype(np.float32))
+    kp = -(-K // 64) * 64
+    Xp = np.zeros((M, kp), np.float32)
+    Xp[:, :K] = X
+    dX = G.to_dev_bf16(Xp)
+    dW = torch.from_numpy(G.tile_bits(gen.to_bf16_bits(Wt)).view(np.int16)).cuda()
+    ref = X.astype(np.float64) @ Wt.astype(np.float64).T
+    ncol = N
+    if epi == "swiglu":
+        ncol = N // 2
+        idx = np.arange(ncol)
+        ref = silu(ref[:, (idx // 16) * 32 + idx % 16]) * ref[:, (idx // 16) * 32 + 16 + idx % 16]
+    R = gen.round_to_bf16(rng.standard_normal((M, ncol)).astype(np.float32))
+    if epi == "resid":
+        ref = R + ref
+
+    def run(rows):
+        Y = G.to_dev_bf16(R[rows]) if epi == "resid" else torch.zeros(
+            (len(R[rows]), ncol), dtype=torch.float32 if epi == "f32" else torch.bfloat16, device="cuda")
+        x = dX[rows].contiguous()
+        hs.hs_k_gemm(x.data_ptr(), kp, dW.data_ptr(), Y.data_ptr(), ncol,
+                     Y.data_ptr() if epi == "resid" else 0, ncol, len(x), N, K, epi, G.stream_ptr())
+        torch.cuda.synchronize()
+        return Y.cpu().numpy() if epi == "f32" else G.from_dev_bf16(Y)
+
+    out = run(slice(0, M))
+    assert np.array_equal(out, run(slice(0, M)))
+    # one bf16 rounding of the result (2^-9 of it) and float32 sums
+    assert np.abs(out - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
+
+
 def test_gemm_small_batches_from_two_streams(monkeypatch):
     """17 to 64 rows, split over workgroups, from two threads with a stream each:
     every result has the bits of the same call made alone."""
