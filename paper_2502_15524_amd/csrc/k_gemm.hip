@@ -16,7 +16,8 @@
 //  * gemm_ring   - prefill: BN x BM x 64 tiles copied straight into an LDS ring
 //                  of NS stages, 8 waves, 16x16x32 bf16 MFMA, XCD-aware order;
 //                  256-token tiles run a ping-pong main loop.
-//  * gemm_skinny - decode (M <= 16 tokens): HBM-bound weight streaming, 2 to
+//  * gemm_skinny - decode (M <= 16 tokens; up to 64 of a small matrix, 16 to a
+//                  workgroup): HBM-bound weight streaming, 2 to
 //                  16 waves split K inside a workgroup, reduced through LDS in
 //                  a fixed order (deterministic).
 #include "hs_device.h"
@@ -722,7 +723,7 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 
 // ------------------------------------------------------------ skinny (decode)
 //
-// A workgroup owns 16 * NF weight rows and all M <= 16 tokens; its WV waves
+// A workgroup owns 16 * NF weight rows and 16 tokens (all, up to 16); its WV waves
 // split the 64-column slabs of K. For one slab, the 2 NF row blocks of the
 // workgroup are adjacent 1 KiB blocks. Each is read by one wave-wide 16-byte
 // load with lane L taking bytes [16 L, 16 L + 16) (a whole block per
@@ -775,6 +776,7 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
       return pull16(a.pull.host, a.pull.dev, a.pull.n16, blockIdx.x * 64 * WV + threadIdx.x);
   }
   const int n0 = ((int)blockIdx.x - pb) * 16 * NF;
+  const int mb = blockIdx.y * 16;  // first token
   const int kp = (a.K + 63) & ~63;
   const int nslab = kp / 64;
   const int sq = (nslab + WV - 1) / WV;  // slabs per wave
@@ -812,7 +814,7 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
   int xoff[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int m = XS ? 8 * i + (lane >> 3) : fr;
+    const int m = mb + (XS ? 8 * i + (lane >> 3) : fr);
     const int chunk = XS ? (lane & 7) ^ (lane >> 3) : 4 * i + g;
     xoff[i] = m < a.M ? m * (int)a.ldx * 2 + chunk * 16 : kPast;
   }
@@ -929,8 +931,8 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
 #pragma unroll
       for (int i = 0; i < PAIR; ++i) o[i] *= inv;
     }
-    if constexpr (EPI == EPI_SWIGLU) store_swiglu(a, fr, n0 / 2 + 16 * p + fq, o[0], o[1]);
-    else store4<EPI>(a, fr, n0 + 16 * p + fq, o[0]);
+    if constexpr (EPI == EPI_SWIGLU) store_swiglu(a, mb + fr, n0 / 2 + 16 * p + fq, o[0], o[1]);
+    else store4<EPI>(a, mb + fr, n0 + 16 * p + fq, o[0]);
   }
 }
 
@@ -940,7 +942,7 @@ namespace {
 
 template <int NF, int WV, bool NORM, int XS>
 hipError_t dispatch_skinny_norm(const GemmArgs& a, int epi, hipStream_t s) {
-  const dim3 grid((a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV));
+  const dim3 grid((a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV), (a.M + 15) / 16);
   const dim3 blk(64 * WV);
   switch (epi) {
     case EPI_STORE:
@@ -1115,12 +1117,23 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
   const double bytes = 2.0 * ((double)a.M * a.K + (double)a.N * a.K) + out_bytes;
   hipError_t e;
   bool split = false;
-  // HS_GEMM_CFG="<tile>[,dp|,sk[<ways>]][,g<n>]" forces a choice of
+  // HS_GEMM_CFG="skinny" or "<tile>[,dp|,sk[<ways>]][,g<n>]" forces a choice of
   // kernel above 16 rows: tile, whole or split tiles, tile group (tuning only;
   // read on every call so that a sweep can change it between calls).
   const char* force_cfg = getenv("HS_GEMM_CFG");
   const bool forced = force_cfg && *force_cfg;
-  if (a.M <= 16) {
+  // 17 to 64 rows of a small matrix: the decode kernel too, 16 rows to a
+  // workgroup, while all its passes read at most 32 MiB of weights (from L2
+  // after the first). The tiles have too few workgroups there. MI355X, decode
+  // kernel / best tiles, us: 17 x 256 x 688 3.3 / 5.4, 17 x 1024 x 1024 3.7 / 6.4,
+  // 64 x 1024 x 4096 7.1 / 8.8, 17 x 3072 x 2048 (24 MiB) 6.2 / 7.9, 64 x 2048 x 2048
+  // (32 MiB) 7.5 / 8.1; above, 33 x 3072 x 2048 (36 MiB) 9.5 / 8.0, 17 x 4096 x 4096
+  // (64 MiB) 13.2 / 11.7. SwiGLU's two waves a workgroup gain nothing (17 x 1376 x
+  // 256 3.6 / 3.6, 64 x 2752 x 512 5.7 / 5.1), and a QKV projection with RoPE would
+  // need a second launch.
+  const bool few = a.M <= 64 && (epi == EPI_STORE || epi == EPI_RESID || epi == EPI_F32) &&
+                   (uint64_t)a.N * kp * 2 * ((a.M + 15) / 16) <= (32ull << 20);
+  if (a.M <= 16 || (forced ? !strcmp(force_cfg, "skinny") && a.M <= 64 : few)) {
     // a QKV projection with RoPE runs as a plain (head-order) store followed
     // by the rotation pass
     const int pe = epi == EPI_QKV_ROPE ? EPI_STORE : epi;

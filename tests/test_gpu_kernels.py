@@ -180,13 +180,16 @@ def test_gemm_tile_configurations(cfg, M, N, K, epi, monkeypatch):
     assert np.abs(outs[0] - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
 
 
-# 17 to 64 rows of matrices whose tiles stay whole or are split two to six ways.
-@pytest.mark.parametrize("M,N,K,epi", [
-    (17, 256, 688, "resid"), (33, 272, 256, "store"), (64, 400, 712, "f32"),
-    (48, 4112, 320, "resid"),
-    (64, 2048, 2048, "resid"), (64, 2064, 2048, "resid"),
-    (17, 1376, 256, "swiglu"), (33, 2048, 5632, "resid"), (64, 1024, 4096, "swiglu")])
-def test_gemm_17_to_64_rows(M, N, K, epi):
+# 17 to 64 rows of matrices on both sides of the choice between the decode kernel
+# (16 rows to a workgroup: up to 32 MiB of weights over all passes) and tiles,
+# whole or split up to six ways. On the decode kernel's side a row has the bits it
+# has in a call of up to 16 rows.
+@pytest.mark.parametrize("M,N,K,epi,decode", [
+    (17, 256, 688, "resid", True), (33, 272, 256, "store", True), (64, 400, 712, "f32", True),
+    (48, 4112, 320, "resid", True),     # more row tiles than CUs: two per workgroup
+    (64, 2048, 2048, "resid", True), (64, 2064, 2048, "resid", False),
+    (17, 1376, 256, "swiglu", False), (33, 2048, 5632, "resid", False), (64, 1024, 4096, "swiglu", False)])
+def test_gemm_17_to_64_rows(M, N, K, epi, decode):
     torch = G.torch()
     hs = _hs()
     rng = np.random.default_rng(M + N + K)
@@ -220,6 +223,9 @@ def test_gemm_17_to_64_rows(M, N, K, epi):
     assert np.array_equal(out, run(slice(0, M)))
     # one bf16 rounding of the result (2^-9 of it) and float32 sums
     assert np.abs(out - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
+    if decode:
+        for m in range(0, M, 16):
+            assert np.array_equal(out[m:m + 16], run(slice(m, min(M, m + 16)))), m
 
 
 def test_gemm_small_batches_from_two_streams(monkeypatch):
