@@ -1148,13 +1148,16 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     // four while that fills three quarters of the CUs (13B 25.4 and, at 16
     // tokens, 25.1 against 26.4 with two). Gate/up runs two waves of four row
     // tiles, of two where four leave fewer than 1.5 workgroups per CU (8B 35.7,
-    // four waves 39.1; 7B at 16 tokens 30.2 against 32.7); the LM head two waves
-    // over as many row tiles as keep about a thousand workgroups. Two or
-    // four slabs requested ahead per wave instead of one were 1-10 % slower
-    // nearly everywhere: the waves of a CU keep enough in flight. Activations
-    // are staged from 8 tokens on in the o and down projections, which take no
-    // norm. WV depends on the shape only, never on M, so that a token's result (its k order) does
-    // not depend on how many tokens share the call.
+    // four waves 39.1; 7B at 16 tokens 30.2 against 32.7). Up to one workgroup of
+    // four row tiles per CU it runs four waves (K = 4096, two waves / four: 8192
+    // wide 24.2 / 15.2, 14336 25.9 / 21.6; above, 17408 at 8 tokens 27.8 / 28.4,
+    // 18432 27.6 / 29.2), of four where that nearly fills the CUs (16384: of two
+    // 25.3, of four 24.1); the LM head two waves over as many row tiles as keep about a thousand
+    // workgroups. Two or four slabs requested ahead per wave instead of one were
+    // 1-10 % slower nearly everywhere: the waves of a CU keep enough in flight.
+    // Activations are staged from 8 tokens on in the o and down projections, which
+    // take no norm. WV depends on the shape only, never on M, so that a token's
+    // result (its k order) does not depend on how many tokens share the call.
     // HS_SKINNY_CFG="<NF>,1,<WV>[,<XS>]" forces a choice (tuning only; read on
     // every call so that a sweep can change it between calls).
     const char* force = getenv("HS_SKINNY_CFG");
@@ -1164,6 +1167,7 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
       while (nf < 8 && a.N / (16 * nf) > 1100) nf *= 2;
     } else if (pe == EPI_SWIGLU) {
       if (a.N / 64 >= cus + cus / 2) nf = 4;
+      else if (a.N / 64 <= cus) wv = 4, nf = a.N / 64 > cus * 7 / 8 ? 4 : 2;
     } else if (pe == EPI_RESID) {
       xs = a.M >= 8;
       if (a.N / 16 > cus) wv = 8;
