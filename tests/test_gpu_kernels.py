@@ -146,7 +146,9 @@ def test_gemm_ping_pong_edges(cfg, M, N, K, epi, monkeypatch):
 @pytest.mark.parametrize("cfg", [f"{t},{m}" for t in ("64x64", "128x64", "128x128", "192x128", "256x128")
                                  for m in ("dp", "sk")])
 @pytest.mark.parametrize("M,N,K,epi", [(17, 16, 64, "f32"), (65, 272, 512, "resid"), (33, 400, 712, "f32"),
-                                       (129, 96, 1088, "swiglu"), (200, 336, 640, "store")])
+                                       (129, 96, 1088, "swiglu"), (200, 336, 640, "store"),
+                                       # nine workgroups a tile: the partials come in two or three rounds
+                                       (100, 256, 2304, "resid")])
 def test_gemm_tile_configurations(cfg, M, N, K, epi, monkeypatch):
     torch = G.torch()
     hs = _hs()
@@ -284,12 +286,17 @@ def test_gemm_small_batches_from_two_streams(monkeypatch):
             assert np.array_equal(outs[t][n].cpu().numpy(), alone[i]), (t, n, i)
 
 
-# 7B-shape projections at a 512-token prompt: few output tiles, so their k
-# ranges are split across workgroups (stream-K). Rows are sampled for the
-# float64 reference; two calls must agree bitwise.
-@pytest.mark.parametrize("N,K,epi", [(12288, 4096, "store"), (4096, 4096, "resid"),
-                                     (22016, 4096, "swiglu"), (4096, 11008, "resid")])
-def test_gemm_split_k_shapes(N, K, epi):
+# Projections of 7B and 8B shapes at a 512-token prompt: with the tiles that the
+# library chooses (whole ones for QKV, o and gate/up; down split two ways) and with
+# split tiles forced. Rows are sampled for the float64 reference; two calls must
+# agree bitwise.
+@pytest.mark.parametrize("N,K,epi,cfg", [
+    (12288, 4096, "store", ""), (4096, 4096, "resid", ""), (22016, 4096, "swiglu", ""), (4096, 11008, "resid", ""),
+    (6144, 4096, "store", "192x128,sk"), (4096, 4096, "resid", "128x128,sk"),
+    (5504, 4096, "swiglu", "256x128,sk"), (4096, 11008, "resid", "256x128,sk")])
+def test_gemm_split_k_shapes(N, K, epi, cfg, monkeypatch):
+    if cfg:
+        monkeypatch.setenv("HS_GEMM_CFG", cfg)
     torch = G.torch()
     hs = _hs()
     M = 512
@@ -422,6 +429,80 @@ def test_attn_prefill_row_sums_are_not_rounded(lens, nh, nkv, d):
         # columns and kv heads of 32 rows or more: 3e-5 or less; a rounded sum is
         # off by 0.36 % n p / (1 + n p), 7e-4 or more
         assert abs(err.mean()) <= 2.5e-4, (i, err.mean())
+
+
+# Both forms of the prefill attention (four heads: 64-query tiles; more: 128) on
+# values that a softmax must keep to where they belong: against the same call
+# without them, bitwise.
+@pytest.mark.parametrize("lens,nh,nkv,d", [([200, 130], 4, 2, 128), ([200, 130], 40, 20, 128),
+                                           ([60, 33], 4, 2, 128), ([200, 130], 4, 2, 64), ([300, 130], 48, 24, 64)])
+@pytest.mark.parametrize("what", ["nan key", "inf key", "inf value"])
+def test_attn_prefill_non_finite_stays_where_it_is(lens, nh, nkv, d, what):
+    torch = G.torch()
+    hs = _hs()
+    rng = np.random.default_rng(nh + d)
+    T = sum(lens)
+    cu = [0] + [int(x) for x in np.cumsum(lens)]
+    qkv = (rng.standard_normal((T, (nh + 2 * nkv) * d)) * 1.5).astype(np.float32)
+
+    def run(x):
+        out = torch.zeros((T, nh * d), dtype=torch.bfloat16, device="cuda")
+        dx = torch.from_numpy(x).cuda().bfloat16()
+        hs.hs_k_attn_prefill(dx.data_ptr(), out.data_ptr(), cu, nh, nkv, d, G.stream_ptr())
+        torch.cuda.synchronize()
+        return G.from_dev_bf16(out).reshape(T, nh, d)
+
+    clean = run(qkv)
+    assert np.isfinite(clean).all()
+    bad = qkv.copy()
+    j, kh = lens[0] - 20, 1                 # a key of the first sequence, one kv head
+    col = (nh + kh) * d if "key" in what else (nh + nkv + kh) * d
+    bad[j, col] = np.nan if what == "nan key" else np.inf
+    got = run(bad)
+    mine = np.zeros(nh, bool)
+    mine[kh * (nh // nkv):(kh + 1) * (nh // nkv)] = True
+    assert np.array_equal(got[:, ~mine], clean[:, ~mine])
+    assert np.array_equal(got[cu[1]:], clean[cu[1]:])
+    # queries before the key do not see it; a value's column also reaches the
+    # queries of its own 64-key block (0 times infinity)
+    first = j if "key" in what else j // 64 * 64
+    assert np.array_equal(got[:first], clean[:first])
+    if what == "nan key":
+        assert np.isnan(got[j:cu[1], mine]).all()
+    elif what == "inf value":
+        assert not np.isfinite(got[j:cu[1], mine, 0]).any()
+        assert np.array_equal(got[:cu[1], mine, 1:], clean[:cu[1], mine, 1:])
+    else:                                   # a score of +inf gives NaN, one of -inf a weight of zero
+        up = qkv[j:cu[1], :nh * d].reshape(-1, nh, d)[:, mine, 0] > 0
+        assert np.isnan(got[j:cu[1], mine][up]).all() and np.isfinite(got[j:cu[1], mine][~up]).all()
+
+
+@pytest.mark.parametrize("lens,nh,nkv,d", [([300, 64], 4, 2, 128), ([300, 700], 24, 12, 128), ([300, 700], 32, 8, 64)])
+def test_attn_prefill_large_scores(lens, nh, nkv, d):
+    """Scores of hundreds to thousands (a row's weight is on one or two keys) and
+    rows of equal scores, in both forms."""
+    torch = G.torch()
+    hs = _hs()
+    rng = np.random.default_rng(nh + 3 * d)
+    T = sum(lens)
+    cu = [0] + [int(x) for x in np.cumsum(lens)]
+    qkv = rng.standard_normal((T, (nh + 2 * nkv) * d)).astype(np.float32)
+    qkv[:, :(nh + nkv) * d] *= 30
+    qkv[::7, :nh * d] = 0
+    qkv = gen.round_to_bf16(qkv)
+    out = torch.zeros((T, nh * d), dtype=torch.bfloat16, device="cuda")
+    hs.hs_k_attn_prefill(G.to_dev_bf16(qkv).data_ptr(), out.data_ptr(), cu, nh, nkv, d, G.stream_ptr())
+    torch.cuda.synchronize()
+    got = G.from_dev_bf16(out)
+    q, k, v = (x.astype(np.float64) for x in np.split(qkv, [nh * d, (nh + nkv) * d], axis=1))
+    q, k, v = q.reshape(T, nh, d), k.reshape(T, nkv, d), v.reshape(T, nkv, d)
+    for i, n in enumerate(lens):
+        s = slice(cu[i], cu[i + 1])
+        ref = attention(q[s], k[s], v[s], np.arange(n), np.arange(n))
+        # float32 scores of up to 1e5 are good to 0.01: a weight beside a close
+        # second is off by as much, everything else by its bf16 rounding
+        err = np.abs(got[s] - ref).max()
+        assert err <= 2e-2 * np.abs(ref).max() + 1e-3, (i, err)
 
 
 def test_attn_prefill_from_three_threads():

@@ -126,6 +126,39 @@ def test_stage_boundary_hidden_matches_oracle(env):
     assert G.rel_fro(got, ref) <= 1e-2
 
 
+@pytest.mark.parametrize("lens,cfg", [([17], "64x64,sk"), ([33, 20], "64x64,sk"), ([64], "128x64,sk"),
+                                      ([40], "skinny"), ([100, 60], "128x128,sk"), ([150], "192x128,sk"),
+                                      ([200, 31], "256x128,sk")])
+def test_split_projections_rotate_and_append(lens, cfg, monkeypatch):
+    """One layer of a model whose projections split up to four ways (1024 wide):
+    hidden states and appended keys and values against the oracle, for every
+    tile that can be split (QKV with RoPE and cache append in its epilogue
+    among them) and for the decode kernel above 16 rows."""
+    from paper_2502_15524_amd import hs, pipeline
+    from workloads.configs import ModelCfg
+    torch = G.torch()
+    m = ModelCfg("split-test", 3, 1024, 8, 4, 128, 1408, 512)
+    monkeypatch.setenv("HS_GEMM_CFG", cfg)
+    T = sum(lens)
+    img = pipeline.pinned_image(m, 1, 2)
+    st = pipeline.Stage(m, 1, 2, max_seqs=4, max_ctx=256, max_batch_tokens=256)
+    st.load(img)
+    x = gen.round_to_bf16(np.random.default_rng(T).standard_normal((T, m.hidden)).astype(np.float32))
+    out = torch.zeros((T, m.hidden), dtype=torch.bfloat16, device="cuda")
+    ids = list(range(len(lens)))
+    st.prefill(ids, lens, G.to_dev_bf16(x).data_ptr(), out.data_ptr(), 0, G.stream_ptr())
+    torch.cuda.synchronize()
+    ost = OStage(m, SyntheticWeights(m), 1, 2)
+    ref = ost.prefill(ids, lens, x)
+    assert G.rel_fro(G.from_dev_bf16(out), ref) <= 1e-2
+    _, kv = kvblob.parse(_export(st, ids).cpu().numpy().tobytes())
+    for i in ids:
+        for got, want in zip(kv[i][1:], ost.kv[i][1]):
+            got = gen.bf16_bits_to_f32(got[0])
+            assert got.shape == want.shape and np.abs(got - want).max() <= 2e-2 * np.abs(want).max()
+    st.close()
+
+
 def test_causality_bitwise(env):
     st = make(env, 0, 1)
     t1 = gen.tokens(CFG.vocab, 100, 77)
