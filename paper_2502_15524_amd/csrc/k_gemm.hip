@@ -1169,9 +1169,9 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
       if (a.N / 64 >= cus + cus / 2) nf = 4;
       else if (a.N / 64 <= cus) wv = 4, nf = a.N / 64 > cus * 7 / 8 ? 4 : 2;
     } else if (pe == EPI_RESID) {
-      xs = a.M >= 8;
       if (a.N / 16 > cus) wv = 8;
-      else nf = 1, wv = 16, xs += a.M > 12;
+      else nf = 1, wv = 16;
+      if (!a.norm_gain && a.M >= 8) xs = nf == 1 && a.M > 12 ? 2 : 1;
     } else if (pe == EPI_STORE) {
       wv = a.N <= 8192 ? 8 : 4;
       if (a.N % 48 == 0 && a.N / 48 <= cus && a.N / 48 > cus * 3 / 4) nf = 3, wv = 16;

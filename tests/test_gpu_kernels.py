@@ -726,7 +726,9 @@ def test_rmsnorm(rows, hidden):
 @pytest.mark.parametrize("M,N,K,epi", [
     (1, 12288, 4096, "store"), (8, 22016, 4096, "swiglu"), (16, 28672, 4096, "swiglu"),
     (12, 6144, 4096, "store"), (16, 12288, 4096, "store"), (5, 1536, 256, "resid"),
-    (3, 512, 64, "f32"), (16, 1376, 320, "swiglu")])
+    (3, 512, 64, "f32"), (16, 1376, 320, "swiglu"),
+    # the residual epilogue stages its activations from 8 rows on, but not under a norm
+    (8, 5120, 256, "resid"), (16, 512, 320, "resid"), (13, 4096, 256, "resid")])
 def test_gemm_rmsnorm(M, N, K, epi):
     torch = G.torch()
     hs = _hs()
