@@ -45,6 +45,12 @@ __device__ __forceinline__ int qk_col(const GemmArgs& a, int n) {
   return (n - d) + ((d >> 4) & 1) * (a.rope_d >> 1) + (d >> 5) * 16 + (d & 15);
 }
 
+// bytes from X to the end of its last row's k range, whatever the row stride
+// (rows may overlap or repeat: ldx below K)
+__device__ __forceinline__ uint64_t x_bytes(const GemmArgs& a, int kp) {
+  return ((uint64_t)(a.M - 1) * a.ldx + kp) * 2;
+}
+
 template <int EPI>
 __device__ __forceinline__ void store4(const GemmArgs& a, int m, int f, const f32x4_v& v) {
   if (m >= a.M || f >= a.N) return;
@@ -478,7 +484,7 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
 
   const int kp = (a.K + 63) & ~63;
   const v4i_t rw = buf_rsrc(a.W, (uint64_t)a.N * kp * 2);
-  const v4i_t rx = buf_rsrc(a.X, (uint64_t)a.M * a.ldx * 2);
+  const v4i_t rx = buf_rsrc(a.X, x_bytes(a, kp));
   const int lrow = lane / CPR;
   const int lchunk = chunk_pos<CPR>(lrow, lane % CPR);  // row base is a multiple of RPI
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -796,7 +802,7 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(a.W), 0, (int)((int64_t)a.N * kp * 2), kRsrcWord3);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<bf16_t*>(a.X), 0, (int)((int64_t)a.M * a.ldx * 2), kRsrcWord3);
+      const_cast<bf16_t*>(a.X), 0, (int)x_bytes(a, kp), kRsrcWord3);
   const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(NORM ? a.norm_gain : a.X), 0, a.K * 2, kRsrcWord3);
   // instruction (f, h) of a slab reads row block n0 / 8 + 2 f + h (N % 16 == 0,
@@ -1106,7 +1112,8 @@ hipError_t gemm(const GemmArgs& a, int epi, hipStream_t s, LaunchInfo* info) {
     return hipErrorInvalidValue;
   if (!pull_ok(a.pull) || (a.pull.n16 && (a.M > 16 || !a.norm_gain))) return hipErrorInvalidValue;
   // 32-bit byte offsets in the buffer loads
-  if ((uint64_t)a.N * kp * 2 >= (1ull << 31) || (uint64_t)a.M * a.ldx * 2 >= (1ull << 31))
+  if ((uint64_t)a.N * kp * 2 >= (1ull << 31) || (uint64_t)a.M * a.ldx * 2 >= (1ull << 31) ||
+      ((uint64_t)(a.M - 1) * a.ldx + kp) * 2 >= (1ull << 31))
     return hipErrorInvalidValue;
 
   static thread_local char name[64];

@@ -105,6 +105,32 @@ def test_gemm_staged_activations_bitwise(M, N, K):
     assert np.abs(outs[1] - ref).max() <= 8e-3 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("M,ldx", [(1, 0), (5, 0), (9, 64), (16, 8), (40, 0), (64, 64), (100, 8), (300, 64)])
+@pytest.mark.parametrize("epi", ["f32", "swiglu"])
+def test_gemm_overlapping_rows(M, ldx, epi):
+    """Rows of X nearer to each other than K (a sliding window), or all the same."""
+    torch = G.torch()
+    hs = _hs()
+    N, K = 288, 512
+    rng = np.random.default_rng(M + ldx)
+    flat = gen.round_to_bf16(rng.standard_normal((M - 1) * ldx + K).astype(np.float32))
+    Wt = gen.round_to_bf16((rng.standard_normal((N, K)) * 0.05).astype(np.float32))
+    X = np.stack([flat[m * ldx:m * ldx + K] for m in range(M)])
+    ref = X.astype(np.float64) @ Wt.astype(np.float64).T
+    ncol = N
+    if epi == "swiglu":
+        ncol = N // 2
+        idx = np.arange(ncol)
+        ref = silu(ref[:, (idx // 16) * 32 + idx % 16]) * ref[:, (idx // 16) * 32 + 16 + idx % 16]
+    dX = G.to_dev_bf16(flat)
+    dW = torch.from_numpy(G.tile_bits(gen.to_bf16_bits(Wt)).view(np.int16)).cuda()
+    Y = torch.zeros((M, ncol), dtype=torch.float32 if epi == "f32" else torch.bfloat16, device="cuda")
+    hs.hs_k_gemm(dX.data_ptr(), ldx, dW.data_ptr(), Y.data_ptr(), ncol, 0, ncol, M, N, K, epi, G.stream_ptr())
+    torch.cuda.synchronize()
+    out = Y.cpu().numpy() if epi == "f32" else G.from_dev_bf16(Y)
+    assert np.abs(out - ref).max() <= (1e-5 if epi == "f32" else 8e-3) * np.abs(ref).max()
+
+
 # The ping-pong main loop at its edges: one, two, three and four 64-k slabs
 # (its peeled ends), a K that is no multiple of 64, rows and columns one past,
 # one short of and far from a tile's end.
