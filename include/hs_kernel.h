@@ -112,8 +112,8 @@ hs_status hs_k_attn_decode_rope(const void* qkv, int64_t ldqkv, void* pool,
  * out: device int32 [n_rows]. Requires n_rows >= 1 and n_cols >= 1 with
  * n_cols % 4 == 0 (HS_EINVAL otherwise). NaN entries never win; a row of
  * NaN only gives 0x7FFFFFFF. The call allocates a small device buffer for
- * the per-chunk candidates, launches the two passes on `stream`, waits for
- * them and frees the buffer. */
+ * the per-chunk candidates, launches on `stream` (one pass up to 4096 columns,
+ * two above), waits for the result and frees the buffer. */
 hs_status hs_k_argmax(const float* logits, int32_t n_rows, int32_t n_cols, int32_t* out,
                       void* stream);
 

@@ -1133,11 +1133,12 @@ void launch_split(const AttnDecodeArgs& a, float sl, hipStream_t s) {
   // kv heads fastest, so that the eight XCDs (workgroup i runs on XCD i mod 8)
   // share every split of every sequence. With the splits fastest and a multiple
   // of eight of them, an XCD had the same splits of all sequences, and those
-  // with the late splits, which only long sequences have, stood idle. Split
-  // kernel, MI355X, splits -> kv heads fastest: 8B heads, 32 sequences of 256 to
-  // 4096 71.0 -> 54.3 us (5.4 TB/s), 16 of 128 to 2048 20.8 -> 17.5; 13B, 40 of 64
-  // to 1024 99.2 -> 74.5 (6.2 TB/s), 16 of 200 to 3000 104 -> 99; 7B, 8 of about
-  // 1100 24.9 -> 25.8.
+  // with the late splits, which only long sequences have, stood idle. MI355X,
+  // both orders in turn, splits -> kv heads fastest, merge included: 8B heads, 32
+  // sequences of 256 to 4096 74.5 -> 58.6 us, 64 of 100 to 900 43.3 -> 35.3; 13B, 40 of
+  // 64 to 1024 94.3 -> 73.9, 16 of 200 to 3000 99.2 -> 94.6. Equal sequences and split
+  // counts that are no multiple of eight are level (7B, 8 of about 1100 29.0 ->
+  // 28.9; of 62 shapes of 1 to 64 sequences two are 1 % slower, within the spread).
   dim3 grid(a.n_kv_heads * a.call_splits, a.B);
   static const char* force = getenv("HS_DECODE_ATTN");  // "valu" (tuning only)
   if constexpr (D == 128 && G >= 2) {

@@ -185,17 +185,13 @@ struct RTile {
   static constexpr int WN = BN / 2, WM = BM / (NW / 2), TN = WN / 16, TM = WM / 16;
   static constexpr int WI = BN / NW / RPI, XI = BM / NW / RPI;  // instructions per wave
   static constexpr int LPS = WI + XI;          // loads per stage per wave
-  static constexpr int W_BYTES = BN * BK * 2, STAGE = (BN + BM) * BK * 2;
+  static constexpr int W_BYTES = BN * BK * 2;
   static_assert(BK == 64, "weights come in 64-column slabs");
   static_assert(WI >= 1 && XI >= 1 && TM >= 1, "tile too small for the waves");
 };
 
-// position of chunk c of row r inside its row
-template <int CPR>
-__device__ __forceinline__ int chunk_pos(int r, int c) {
-  if constexpr (CPR == 8) return c ^ (r & 7);
-  else return c ^ ((r >> 1) & 3);
-}
+// position of chunk c of row r inside its row of eight
+__device__ __forceinline__ int chunk_pos(int r, int c) { return c ^ (r & 7); }
 
 // Multiply one stage (BK/32 steps of 32 k). Fragment reads are software
 // pipelined against the MFMAs and the order is pinned with scheduling group
@@ -206,9 +202,8 @@ __device__ __forceinline__ int chunk_pos(int r, int c) {
 // come from LDS. Its operands have to be in registers by that barrier, after
 // which any wave may refill the stage: the wave waits for its reads (lgkmcnt)
 // together with its copies.
-template <int CPR>
 __device__ __forceinline__ bf16x8_v lds_frag(const bf16_t* s, int r, int c) {
-  return as_bf16x8(ld16(s + (r * CPR + chunk_pos<CPR>(r, c)) * 8));
+  return as_bf16x8(ld16(s + (r * 8 + chunk_pos(r, c)) * 8));
 }
 
 // How many row tiles ahead of its MFMAs a wave reads the A fragments: three
@@ -227,17 +222,17 @@ __device__ __forceinline__ void ring_stage(f32x4_v (&acc)[TN][TM], bf16x8_v (&a)
                                            const bf16_t* sx, int wn, int wm, int fr, int g,
                                            bool pending, Dma&& dma) {
   using T = RTile<BN, BM, BK, NS>;
-  constexpr int CPR = T::CPR, KS = BK / 32, NT = TN * KS;
+  constexpr int KS = BK / 32, NT = TN * KS;
   constexpr int MASK_MFMA = 0x008, MASK_DS_READ = 0x100;
   // row tile t of the stage (t = ks TN + i) uses A slot t mod (PD + 1); the
   // deferred last one must not share a slot with the next stage's first PD
   static_assert(KS == 2 && NT % (PD + 1) == 0, "A fragment slots");
   constexpr int LAST = (NT - 1) % (PD + 1);
   auto read_a = [&](int t) {
-    a[t % (PD + 1)] = lds_frag<CPR>(sw, wn * T::WN + (t % TN) * 16 + fr, (t / TN) * 4 + g);
+    a[t % (PD + 1)] = lds_frag(sw, wn * T::WN + (t % TN) * 16 + fr, (t / TN) * 4 + g);
   };
 #pragma unroll
-  for (int j = 0; j < TM; ++j) b[0][j] = lds_frag<CPR>(sx, wm * T::WM + j * 16 + fr, g);
+  for (int j = 0; j < TM; ++j) b[0][j] = lds_frag(sx, wm * T::WM + j * 16 + fr, g);
 #pragma unroll
   for (int t = 0; t < PD; ++t) read_a(t);
   __builtin_amdgcn_sched_group_barrier(MASK_DS_READ, TM + PD, 0);
@@ -260,7 +255,7 @@ __device__ __forceinline__ void ring_stage(f32x4_v (&acc)[TN][TM], bf16x8_v (&a)
     if (rb) {
 #pragma unroll
       for (int j = 0; j < TM; ++j)
-        b[(ks + 1) & 1][j] = lds_frag<CPR>(sx, wm * T::WM + j * 16 + fr, (ks + 1) * 4 + g);
+        b[(ks + 1) & 1][j] = lds_frag(sx, wm * T::WM + j * 16 + fr, (ks + 1) * 4 + g);
     }
     if (t == NT - 1) break;  // deferred to the next stage (or the end)
 #pragma unroll
@@ -463,7 +458,7 @@ __device__ __forceinline__ void pp_mainloop(f32x4_v (&acc)[TN][TM], const GemmAr
 
 // NS stages of both operands: the loads of slab j + NS - 1 are in flight while
 // slab j is multiplied. PP: the ping-pong main loop instead.
-template <int BN, int BM, int NS, int SPR, bool SK, int EPI, bool PP>
+template <int BN, int BM, int NS, bool SK, int EPI, bool PP>
 __global__ __launch_bounds__(64 * kRingWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_ring(GemmArgs a, GemmSched sc) {
   constexpr int BK = 64, NW = kRingWaves;
@@ -486,7 +481,7 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
   const v4i_t rw = buf_rsrc(a.W, (uint64_t)a.N * kp * 2);
   const v4i_t rx = buf_rsrc(a.X, x_bytes(a, kp));
   const int lrow = lane / CPR;
-  const int lchunk = chunk_pos<CPR>(lrow, lane % CPR);  // row base is a multiple of RPI
+  const int lchunk = chunk_pos(lrow, lane % CPR);  // row base is a multiple of RPI
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int vw = lane * 16;
   const int sw_slab = (a.N / 8) * 1024;
@@ -564,10 +559,9 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
       else
         dma16(rx, vx[q - T::WI], kt * BK * 2, lds_x + stage * X_BYTES + (q - T::WI) * 1024);
     };
-    // the loads of a step are spread over the first SPR/4 of the row-tile
-    // steps of the current slab's multiplication
-    constexpr int STEPS = TN * (BK / 32), USE = STEPS * SPR / 4;
-    static_assert(USE >= 1, "spread");
+    // the loads of a step are spread over the row-tile steps of the current
+    // slab's multiplication
+    constexpr int STEPS = TN * (BK / 32);
     // Step j issues the loads of slab j + NS - 1 while it multiplies slab j.
     // The issue is behind a (uniform) branch on purpose: it splits the step
     // into scheduling regions, without which the register allocator shuffles
@@ -592,9 +586,9 @@ void gemm_ring(GemmArgs a, GemmSched sc) {
       const bf16_t* sxs =
           reinterpret_cast<const bf16_t*>(smem + NS * T::W_BYTES + (j % NS) * X_BYTES);
       ring_stage<BN, BM, BK, NS, TN, TM, PD>(acc, fa, fb, sws, sxs, wn, wm, fr, g, j > 0, [&](int step) {
-        if (more && step < USE) {
+        if (more) {
 #pragma unroll
-          for (int q = step * LPS / USE; q < (step + 1) * LPS / USE; ++q) issue(j + AHEAD, q);
+          for (int q = step * LPS / STEPS; q < (step + 1) * LPS / STEPS; ++q) issue(j + AHEAD, q);
         }
       });
       // slab j's stage is refilled, by any wave, right after the barrier: the
@@ -946,64 +940,47 @@ __global__ __launch_bounds__(64 * WV) void gemm_skinny(GemmArgs a) {
 
 namespace {
 
-template <int NF, int WV, bool NORM, int XS>
-hipError_t dispatch_skinny_norm(const GemmArgs& a, int epi, hipStream_t s) {
+// The skinny builds, as (epilogue, rows per workgroup / 16, waves per
+// workgroup, staged activations): the ones the selection in gemm() takes. Those
+// without staging are built with and without the norm.
+#define HS_SKINNY_BUILDS(X)                                                  \
+  X(EPI_F32, 2, 2, 0) X(EPI_F32, 4, 2, 0) X(EPI_F32, 8, 2, 0)               \
+  X(EPI_SWIGLU, 2, 2, 0) X(EPI_SWIGLU, 4, 2, 0) X(EPI_SWIGLU, 2, 4, 0)      \
+  X(EPI_SWIGLU, 4, 4, 0) X(EPI_STORE, 2, 8, 0) X(EPI_STORE, 2, 4, 0)        \
+  X(EPI_STORE, 4, 4, 0) X(EPI_STORE, 3, 16, 0) X(EPI_RESID, 2, 8, 0)        \
+  X(EPI_RESID, 2, 8, 1) X(EPI_RESID, 1, 16, 0) X(EPI_RESID, 1, 16, 1)       \
+  X(EPI_RESID, 1, 16, 2)
+
+template <int EPI, int NF, int WV, int XS>
+hipError_t launch_skinny(const GemmArgs& a, hipStream_t s) {
   const dim3 grid((a.N + 16 * NF - 1) / (16 * NF) + a.pull.blocks(64 * WV), (a.M + 15) / 16);
   const dim3 blk(64 * WV);
-  switch (epi) {
-    case EPI_STORE:
-      hipLaunchKernelGGL((gemm_skinny<NF, EPI_STORE, NORM, WV, XS>), grid, blk, 0, s, a);
-      break;
-    case EPI_RESID:
-      hipLaunchKernelGGL((gemm_skinny<NF, EPI_RESID, NORM, WV, XS>), grid, blk, 0, s, a);
-      break;
-    case EPI_SWIGLU:
-      if constexpr (NF % 2 == 0) {
-        hipLaunchKernelGGL((gemm_skinny<NF, EPI_SWIGLU, NORM, WV, XS>), grid, blk, 0, s, a);
-        break;
-      } else {
-        return hipErrorInvalidValue;
-      }
-    case EPI_F32:
-      hipLaunchKernelGGL((gemm_skinny<NF, EPI_F32, NORM, WV, XS>), grid, blk, 0, s, a);
-      break;
-    default: return hipErrorInvalidValue;
+  if (a.norm_gain) {
+    if constexpr (XS) return hipErrorInvalidValue;
+    else hipLaunchKernelGGL((gemm_skinny<NF, EPI, true, WV, 0>), grid, blk, 0, s, a);
+  } else {
+    hipLaunchKernelGGL((gemm_skinny<NF, EPI, false, WV, XS>), grid, blk, 0, s, a);
   }
   return hipGetLastError();
 }
 
-// The skinny variants, as (rows per workgroup / 16, waves per workgroup,
-// staged activations): the ones the selection in gemm() takes.
-#define HS_SKINNY_BUILDS(X)                                        \
-  X(2, 8, 0) X(2, 4, 0) X(4, 4, 0) X(2, 2, 0) X(4, 2, 0) X(8, 2, 0) \
-  X(1, 16, 0) X(3, 16, 0) X(1, 16, 1) X(1, 16, 2) X(2, 8, 1)
-
-template <int NF, int WV, int XS>
-hipError_t dispatch_epi_skinny(const GemmArgs& a, int epi, hipStream_t s) {
-  if (a.norm_gain) {
-    if constexpr (!XS) return dispatch_skinny_norm<NF, WV, true, 0>(a, epi, s);
-    else return hipErrorInvalidValue;
-  }
-  return dispatch_skinny_norm<NF, WV, false, XS>(a, epi, s);
-}
-
 hipError_t dispatch_skinny(const GemmArgs& a, int epi, int nf, int wv, int xs, hipStream_t s) {
-#define HS_SKINNY_CASE(NF_, WV_, XS_) \
-  if (nf == NF_ && wv == WV_ && xs == XS_) return dispatch_epi_skinny<NF_, WV_, XS_>(a, epi, s);
+#define HS_SKINNY_CASE(EPI_, NF_, WV_, XS_) \
+  if (epi == EPI_ && nf == NF_ && wv == WV_ && xs == XS_) return launch_skinny<EPI_, NF_, WV_, XS_>(a, s);
   HS_SKINNY_BUILDS(HS_SKINNY_CASE)
 #undef HS_SKINNY_CASE
   return hipErrorInvalidValue;
 }
 
-template <int BN, int BM, int NS, int SPR, bool SK, bool PP = false>
+template <int BN, int BM, int NS, bool SK, bool PP = false>
 hipError_t dispatch_ring(const GemmArgs& a, int epi, const GemmSched& sc, int grid, hipStream_t s) {
   const dim3 blk(64 * kRingWaves);
   switch (epi) {
-    case EPI_STORE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_STORE, PP>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_RESID, PP>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_SWIGLU, PP>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_F32: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_F32, PP>), dim3(grid), blk, 0, s, a, sc); break;
-    case EPI_QKV_ROPE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SPR, SK, EPI_QKV_ROPE, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_STORE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SK, EPI_STORE, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_RESID: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SK, EPI_RESID, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SK, EPI_SWIGLU, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SK, EPI_F32, PP>), dim3(grid), blk, 0, s, a, sc); break;
+    case EPI_QKV_ROPE: hipLaunchKernelGGL((gemm_ring<BN, BM, NS, SK, EPI_QKV_ROPE, PP>), dim3(grid), blk, 0, s, a, sc); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1050,15 +1027,15 @@ const RingCfg kRing[] = {
 // kernel, whose workgroups each read all activations from L2 unpipelined).
 template <int BN, int BM, int NS>
 hipError_t dispatch_split(const GemmArgs& a, int epi, const GemmSched& sc, int grid, hipStream_t s) {
-  return sc.split > 1 ? dispatch_ring<BN, BM, NS, 4, true>(a, epi, sc, grid, s)
-                      : dispatch_ring<BN, BM, NS, 4, false>(a, epi, sc, grid, s);
+  return sc.split > 1 ? dispatch_ring<BN, BM, NS, true>(a, epi, sc, grid, s)
+                      : dispatch_ring<BN, BM, NS, false>(a, epi, sc, grid, s);
 }
 
 hipError_t launch_ring(const RingCfg& c, const GemmArgs& a, int epi, const GemmSched& sc,
                        int grid, hipStream_t s) {
   switch (c.bn * 1000 + c.bm) {
-    case 256256: return dispatch_ring<256, 256, 2, 2, false, true>(a, epi, sc, grid, s);
-    case 192256: return dispatch_ring<192, 256, 2, 2, false, true>(a, epi, sc, grid, s);
+    case 256256: return dispatch_ring<256, 256, 2, false, true>(a, epi, sc, grid, s);
+    case 192256: return dispatch_ring<192, 256, 2, false, true>(a, epi, sc, grid, s);
     case 256128: return dispatch_split<256, 128, 3>(a, epi, sc, grid, s);
     case 192128: return dispatch_split<192, 128, 4>(a, epi, sc, grid, s);
     case 128128: return dispatch_split<128, 128, 4>(a, epi, sc, grid, s);
