@@ -249,11 +249,13 @@ def main():
 def gemm_shapes(reps=20, copies=4):
     """The decoder-layer projections of the 7B shape at 512 and 8192 prompt
     tokens and at 1 and 8 decode tokens, and of the 8B-GQA shape at 16 decode
-    tokens, each timed with HIP events over `reps` launches through
-    hs_k_gemm (the library picks the configuration as in a stage) with
-    `copies` weight matrices in rotation, so the weights stream from HBM as in
+    tokens, each captured into a graph of `reps` launches through hs_k_gemm (the
+    library picks the configuration as in a stage; launched one by one from
+    Python the shortest would wait for the host) with weight matrices of at least
+    512 MB and `copies` in rotation, so the weights stream from HBM as in
     a stage; beside them torch.matmul (hipBLASLt) of the same operands, which
-    writes the plain product (no residual read, no SwiGLU halving). Random
+    writes the plain product (no residual read, no SwiGLU halving). The two
+    graphs replay in turn, the medians of seven replays are printed. Random
     bf16 operands (timing only). QKV runs with the plain-store epilogue here;
     in a stage, prompts of more than 16 tokens rotate and append in the QKV
     epilogue and decode batches fold the RMSNorm into QKV and gate/up."""
@@ -272,43 +274,47 @@ def gemm_shapes(reps=20, copies=4):
                 kp = (K + 63) // 64 * 64
                 X = torch.zeros(M, kp, device=dev, dtype=torch.bfloat16)
                 X[:, :K] = torch.randn(M, K, device=dev).bfloat16()
-                Ws = [(torch.randn(N, K, device=dev) * 0.02).bfloat16() for _ in range(copies)]
+                Ws = [(torch.randn(N, K, device=dev) * 0.02).bfloat16()
+                      for _ in range(max(copies, -(-(512 << 20) // (2 * N * K))))]
                 ncol = N // 2 if epi == 2 else N
                 Y = torch.zeros(M, ncol, device=dev, dtype=torch.bfloat16)
+                Z = torch.empty(M, N, device=dev, dtype=torch.bfloat16)
                 R = torch.randn(M, ncol, device=dev).bfloat16()
-                it = [0]
 
-                def ours():
-                    W = Ws[it[0] % copies]
-                    it[0] += 1
+                def ours(W):
                     hs.hs_k_gemm(X.data_ptr(), kp, W.data_ptr(), Y.data_ptr(), ncol,
-                                 R.data_ptr() if epi == 1 else 0, ncol, M, N, K, epi, 0)
+                                 R.data_ptr() if epi == 1 else 0, ncol, M, N, K, epi,
+                                 torch.cuda.current_stream().cuda_stream)
 
-                def theirs():
-                    W = Ws[it[0] % copies]
-                    it[0] += 1
-                    torch.matmul(X[:, :K], W.t())
+                def theirs(W):
+                    torch.matmul(X[:, :K], W.t(), out=Z)
 
-                res = []
+                graphs, times = [], ([], [])
                 for fn in (ours, theirs):
-                    for _ in range(3):
-                        fn()
-                    e0 = torch.cuda.Event(enable_timing=True)
-                    e1 = torch.cuda.Event(enable_timing=True)
+                    fn(Ws[0])
                     torch.cuda.synchronize()
-                    e0.record()
-                    for _ in range(reps):
-                        fn()
-                    e1.record()
-                    torch.cuda.synchronize()
-                    res.append(e0.elapsed_time(e1) / reps * 1e3)
+                    graphs.append(torch.cuda.CUDAGraph())
+                    with torch.cuda.graph(graphs[-1]):
+                        for i in range(reps):
+                            fn(Ws[i % len(Ws)])
+                for _ in range(7):
+                    for g, t in zip(graphs, times):
+                        e0 = torch.cuda.Event(enable_timing=True)
+                        e1 = torch.cuda.Event(enable_timing=True)
+                        g.replay()
+                        e0.record()
+                        g.replay()
+                        e1.record()
+                        torch.cuda.synchronize()
+                        t.append(e0.elapsed_time(e1) / reps * 1e3)
+                res = [sorted(t)[3] for t in times]
                 flops = 2.0 * M * N * K
                 wbytes = 2.0 * N * K
                 rows.append(f"| {model} | {M} | {name} | {N} x {K} | {res[0]:.1f} | "
                             f"{flops / res[0] / 1e6:.0f} | {wbytes / res[0] / 1e3:.0f} | "
                             f"{res[1]:.1f} | {flops / res[1] / 1e6:.0f} |")
                 log(rows[-1])
-                del Ws, X, Y, R
+                del graphs, Ws, X, Y, Z, R
     print("| model | tokens | projection | N x K | hs_k_gemm us | TFLOP/s | weight GB/s | "
           "torch.matmul us | TFLOP/s |")
     print("|---|---|---|---|---|---|---|---|---|")
