@@ -996,7 +996,10 @@ hipError_t dispatch_ring(const GemmArgs& a, int epi, const GemmSched& sc, int gr
 // nine projections of 7B, 8B and 13B shapes at 80 to 512 tokens and seven at
 // 640 to 4096: each configuration's own times within 3-7 % (rms), the choice
 // 0.4 % behind the best configuration of every shape on average and 8 % at
-// worst. Against the choice by per-CU rates before it and the split launches
+// worst. (Up to 64 rows, where it was not fitted, and some of the 64-token tiles'
+// terms came out as zero, it only chooses between those two tiles: over 44 shapes
+// of 17 to 64 rows 0.6 % behind the best of both on average, 11 % at worst, 33 x
+// 15360 x 5120.) Against the choice by per-CU rates before it and the split launches
 // before them, 16 % faster over those shapes: 160 tokens x 15360 x 5120 68.7 ->
 // 42.9 us, 512 x 5120 x 13824 138.9 -> 93.8, 512 x 6144 x 4096 47.6 -> 34.6.
 struct RingCfg {
